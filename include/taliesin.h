@@ -400,7 +400,7 @@ typedef struct tl_chains {
                                a slot is left for it) is keyed as its last
                                block, as TL_KEYS_TAIL does on the host */
 
-/* Keys and lookup, one lane per chain (fewer than 2^24 chains). Without an
+/* Keys and lookup (fewer than 2^24 chains). Without an
  * index: every block's key is written (slots [0, n_c) of each chain) and
  * d_hits[c] = n_c. With an index: the chain stops at its first key that is
  * not in the index; d_hits[c] = the number of leading blocks found, d_keys

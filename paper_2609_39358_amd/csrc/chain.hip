@@ -4,16 +4,14 @@
 // token ids as u32 little-endian), rooted at the namespace digest or at a
 // caller-supplied parent key (Sec. 2.2: state is stored under a fingerprint
 // of the exact input bytes, the model and the tenant; Sec. 5: reuse is of
-// whole blocks at exact positions). A chain is inherently sequential, so one
-// lane walks one chain; the chip's parallelism is across chains. While there
-// are no more chains than SIMDs each chain gets a wavefront of its own (waves
-// on one SIMD share its vector ALU, and a chain's time is its own instruction
-// latency); beyond that, chains share wavefronts, up to 64.
+// whole blocks at exact positions). A chain is inherently sequential; the
+// chip's parallelism is across chains. Up to 16 chains per compute unit get a
+// workgroup of four wavefronts each (k_chain_waves), which divides the work of
+// one chain; beyond that chains share wavefronts, up to 64 (k_chain).
 //
-// The walk probes the device index while it computes: the home slot of key k
-// (64 bytes, one cache line) is requested before key k+1 is computed and
-// inspected after, so the lookup latency hides behind the hash. Key k+1 is
-// kept only once key k is known to be a hit.
+// The walk probes the device index while it computes, so the lookup of key k
+// hides behind the hash of key k+1. Key k+1 is kept only once key k is known
+// to be a hit.
 //
 // Device index: linear probing over 64-byte slots
 //   word 0  tag = first 8 key bytes | 1 (0 = empty)
@@ -35,6 +33,10 @@
 
 namespace {
 
+#ifndef TL_CHAIN_WAVES_PER_CU
+#define TL_CHAIN_WAVES_PER_CU 16  // chains per compute unit up to which each gets a workgroup
+#endif
+
 constexpr uint32_t kMaxProbe = 1024;  // slots a key may sit past its home slot
 constexpr uint32_t kNoSlot = 0xffffffffu;
 constexpr uint64_t kMiss = ~0ull;
@@ -45,13 +47,22 @@ constexpr uint32_t kSlotWords = 8;
 __device__ __forceinline__ uint32_t rotr(uint32_t x, uint32_t n) {
   return __builtin_amdgcn_alignbit(x, x, n);
 }
-__device__ __forceinline__ uint32_t bsig0(uint32_t a) { return rotr(a, 2) ^ rotr(a, 13) ^ rotr(a, 22); }
-__device__ __forceinline__ uint32_t bsig1(uint32_t e) { return rotr(e, 6) ^ rotr(e, 11) ^ rotr(e, 25); }
-__device__ __forceinline__ uint32_t ssig0(uint32_t x) { return rotr(x, 7) ^ rotr(x, 18) ^ (x >> 3); }
-__device__ __forceinline__ uint32_t ssig1(uint32_t x) { return rotr(x, 17) ^ rotr(x, 19) ^ (x >> 10); }
-__device__ __forceinline__ uint32_t ch(uint32_t e, uint32_t f, uint32_t g) { return g ^ (e & (f ^ g)); }
+// gfx950 has any function of three words in one instruction (v_bitop3_b32;
+// the immediate is the function of 0xf0, 0xcc and 0xaa); the compiler forms
+// it from only some of these expressions.
+__device__ __forceinline__ uint32_t xor3(uint32_t a, uint32_t b, uint32_t c) {
+  return (uint32_t)__builtin_amdgcn_bitop3_b32((int)a, (int)b, (int)c, 0x96);
+}
+__device__ __forceinline__ uint32_t pick(uint32_t mask, uint32_t a, uint32_t b) {  // bits of a where mask is set
+  return (uint32_t)__builtin_amdgcn_bitop3_b32((int)mask, (int)a, (int)b, 0xca);
+}
+__device__ __forceinline__ uint32_t bsig0(uint32_t a) { return xor3(rotr(a, 2), rotr(a, 13), rotr(a, 22)); }
+__device__ __forceinline__ uint32_t bsig1(uint32_t e) { return xor3(rotr(e, 6), rotr(e, 11), rotr(e, 25)); }
+__device__ __forceinline__ uint32_t ssig0(uint32_t x) { return xor3(rotr(x, 7), rotr(x, 18), x >> 3); }
+__device__ __forceinline__ uint32_t ssig1(uint32_t x) { return xor3(rotr(x, 17), rotr(x, 19), x >> 10); }
+__device__ __forceinline__ uint32_t ch(uint32_t e, uint32_t f, uint32_t g) { return pick(e, f, g); }
 __device__ __forceinline__ uint32_t maj(uint32_t a, uint32_t b, uint32_t c) {
-  return (a & b) | (c & (a | b));
+  return (uint32_t)__builtin_amdgcn_bitop3_b32((int)a, (int)b, (int)c, 0xe8);
 }
 
 // Rounds R..63 with the working variables passed by value, so that the
@@ -409,6 +420,421 @@ struct ChainArgs {
   uint64_t* handles;
   uint32_t* hits;
 };
+
+// ---- one chain on a workgroup of four wavefronts -------------------------------
+// What bounds a chain is its serial path: a lone wavefront issues one vector
+// instruction every 4.4 cycles (1.86 ns, the same for every instruction the
+// walk uses), so a block costs its instruction count. k_chain below issues
+// about 4,700 per 16-token block (8.7 us), most of them message schedule,
+// padding selection and waits for token loads. Here the serial path holds
+// nothing but the 64 rounds of each compression, and the other wavefronts of
+// the workgroup, each on its own SIMD, feed it through LDS. Measured: one to
+// 256 chains 3.4 us per 16-token block against 8.2 (k_chain), 1,024 chains 4.1
+// against 20.8; each further compression of a block 1.4 us (64-token blocks
+// 7.5 against 21.6):
+//   wave 0  the rounds, ten instructions each (TL_ROUND below)
+//   wave 1  the message schedule of a block's first compression, the only one
+//           that depends on the previous key, published eight words at a time
+//   wave 2  stores the keys and looks them up; a miss stops the others
+//   wave 3  tiles of 64 compressions, one per lane: the schedule plus round
+//           constants of every later compression (they hold tokens and padding
+//           only), and words 8..15 of first compressions
+// Every wait is for a wavefront of the same workgroup (all four are resident)
+// and also ends when wave 2 stops the walk. LDS accesses of one wavefront are
+// performed in order, so a reader that loads a counter and then the data it
+// covers, in one go, may use the data when the counter says so.
+constexpr uint32_t kTileComps = 64;
+constexpr uint32_t kRowWords = 68;  // a tile row: 64 words, padded against bank conflicts
+constexpr uint32_t kRing = 16;      // keys between wave 0 and their readers
+
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+
+// Control words: read together, written one by one.
+enum : uint32_t { kSchedSeq, kKeySeq, kKeyUsed, kStop, kTileReady, kTileDone, kCtlWords = 8 };
+
+struct SeqShared {
+  uint32_t tile[2][kTileComps * kRowWords];
+  uint32_t sched[48];  // K + W for rounds 16..63 of a block's first compression (get_sched)
+  uint32_t ring[kRing][8];
+  uint32_t ctl[kCtlWords];
+};
+
+// LDS accesses that other wavefronts' accesses meet: kept in program order.
+typedef __attribute__((address_space(3))) volatile uint32_t lds_u32;
+typedef __attribute__((address_space(3))) volatile u32x4 lds_u32x4;
+__device__ __forceinline__ uint32_t lds_get(const uint32_t* p) { return *(const lds_u32*)p; }
+__device__ __forceinline__ u32x4 lds_get4(const uint32_t* p) { return *(const lds_u32x4*)p; }
+__device__ __forceinline__ void lds_put(uint32_t* p, uint32_t v) { *(lds_u32*)p = v; }
+__device__ __forceinline__ void lds_put4(uint32_t* p, u32x4 v) { *(lds_u32x4*)p = v; }
+__device__ __forceinline__ uint32_t scalar(uint32_t v) { return __builtin_amdgcn_readfirstlane(v); }
+
+// Waits until control word i reaches `want` (modulo 2^32); false when the walk
+// was stopped.
+template <bool kSleep>
+__device__ __forceinline__ bool wait_for(const SeqShared& s, uint32_t i, uint32_t want) {
+  uint32_t v = scalar(lds_get(&s.ctl[i])), stop = scalar(lds_get(&s.ctl[kStop]));
+  while (((int32_t)(v - want) < 0) & !stop) {
+    if constexpr (kSleep) __builtin_amdgcn_s_sleep(1);
+    v = scalar(lds_get(&s.ctl[i]));
+    stop = scalar(lds_get(&s.ctl[kStop]));
+  }
+  return !stop;
+}
+
+// One round with the working variables split over lanes: lanes 0-3 and 8-11
+// of a row of 16 hold (e, f, g, h), the other eight (a, b, c, d), so that one
+// instruction does a step of Sigma1 and of Sigma0 (shift amounts per lane), or
+// of Ch and of Maj: with u = m ? ~(x ^ y) : x, u ? y : z is Ch(x, y, z) where
+// m = 0 and Maj(x, y, z) where m = ~0. X = Sigma + Ch|Maj + hk with
+// hk = h + K + W in the e-lanes and 0 in the a-lanes; the new e is X + d and
+// the new a is X + the e-lanes' X, the other half's value read with a rotation
+// of the row by 4. w (h and d) becomes the new variable. hk is set for the
+// next round from its h (now z) and its kw. A DPP operand may be read only two
+// wait states after a vector instruction wrote it: the two instructions
+// between X and its rotated use are those, and z and w are older than that.
+#define TL_ROUND(x, y, z, w, kw_next)                                              \
+  "v_alignbit_b32 %[t0], %[" x "], %[" x "], %[s0]\n\t"                             \
+  "v_alignbit_b32 %[t1], %[" x "], %[" x "], %[s1]\n\t"                             \
+  "v_alignbit_b32 %[t2], %[" x "], %[" x "], %[s2]\n\t"                             \
+  "v_bitop3_b32 %[u], %[" x "], %[" y "], %[m] bitop3:0xd2\n\t"                     \
+  "v_bitop3_b32 %[t0], %[t0], %[t1], %[t2] bitop3:0x96\n\t"                         \
+  "v_bitop3_b32 %[u], %[u], %[" y "], %[" z "] bitop3:0xca\n\t"                     \
+  "v_add3_u32 %[t1], %[t0], %[u], %[hk]\n\t"                                        \
+  "v_add_u32_dpp %[" w "], %[" w "], %[t1] row_ror:4 row_mask:0xf bank_mask:0xf\n\t" \
+  "v_add_u32_dpp %[hk], %[" z "], %[" kw_next "] quad_perm:[0,1,2,3] row_mask:0xf bank_mask:0x5\n\t" \
+  "v_add_u32_dpp %[" w "], %[t1], %[t1] row_ror:4 row_mask:0xf bank_mask:0xa\n\t"
+#define TL_ROUND_OPERANDS(...)                                                               \
+  : [a] "+v"(v[0]), [b] "+v"(v[1]), [c] "+v"(v[2]), [d] "+v"(v[3]), [hk] "+v"(hk), [t0] "=&v"(t0), \
+    [t1] "=&v"(t1), [t2] "=&v"(t2), [u] "=&v"(u)                                            \
+  : [s0] "v"(s0), [s1] "v"(s1), [s2] "v"(s2), [m] "v"(m), __VA_ARGS__
+
+// Lane constants and working variables of wave 0.
+struct Rounds {
+  uint32_t s0, s1, s2, m;
+  uint32_t v[4];  // e-lanes: e, f, g, h; a-lanes: a, b, c, d
+  uint32_t hk;    // stays 0 in the a-lanes
+
+  __device__ __forceinline__ void init(uint32_t lane) {
+    const bool a = lane >> 2 & 1;
+    s0 = a ? 2 : 6;
+    s1 = a ? 13 : 11;
+    s2 = a ? 22 : 25;
+    m = a ? 0xffffffffu : 0;
+    hk = 0;
+  }
+  // hk of a compression's first round
+  __device__ __forceinline__ void start(uint32_t kw0) {
+    asm("s_nop 1\n\tv_add_u32_dpp %0, %1, %2 quad_perm:[0,1,2,3] row_mask:0xf bank_mask:0x5"
+        : "+v"(hk) : "v"(v[3]), "v"(kw0));
+  }
+  // Four rounds; k1, k2, k3 and next are the words of the rounds after the
+  // first. After four rounds v is in its first order again.
+  __device__ __forceinline__ void four(uint32_t k1, uint32_t k2, uint32_t k3, uint32_t next) {
+    uint32_t t0, t1, t2, u;
+    asm(TL_ROUND("a", "b", "c", "d", "k1") TL_ROUND("d", "a", "b", "c", "k2") TL_ROUND("c", "d", "a", "b", "k3")
+            TL_ROUND("b", "c", "d", "a", "k4")
+        TL_ROUND_OPERANDS([k1] "v"(k1), [k2] "v"(k2), [k3] "v"(k3), [k4] "v"(next)));
+  }
+  // The first three and the last of four rounds, for a `next` that comes late.
+  __device__ __forceinline__ void three(uint32_t k1, uint32_t k2, uint32_t k3) {
+    uint32_t t0, t1, t2, u;
+    asm(TL_ROUND("a", "b", "c", "d", "k1") TL_ROUND("d", "a", "b", "c", "k2") TL_ROUND("c", "d", "a", "b", "k3")
+        TL_ROUND_OPERANDS([k1] "v"(k1), [k2] "v"(k2), [k3] "v"(k3)));
+  }
+  __device__ __forceinline__ void fourth(uint32_t next) {
+    uint32_t t0, t1, t2, u;
+    asm(TL_ROUND("b", "c", "d", "a", "k4") TL_ROUND_OPERANDS([k4] "v"(next)));
+  }
+};
+
+__device__ __forceinline__ void get8(uint32_t (&out)[8], const uint32_t* p) {
+  const u32x4 a = lds_get4(p), b = lds_get4(p + 4);
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    out[i] = a[i];
+    out[4 + i] = b[i];
+  }
+}
+
+// Eight words of wave 1's schedule: the even ones come first.
+__device__ __forceinline__ void get_sched(uint32_t (&out)[8], const uint32_t* p) {
+  const u32x4 a = lds_get4(p), b = lds_get4(p + 4);
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    out[2 * i] = a[i];
+    out[2 * i + 1] = b[i];
+  }
+}
+
+// Wave 0: the rounds of every compression of the chain, in order.
+__device__ __forceinline__ void seq_rounds(SeqShared& s, const ChainIn& in, const Range& r, const uint32_t (&parent)[8],
+                                           uint32_t lane) {
+  Rounds R;
+  R.init(lane);
+  const bool a_lane = lane >> 2 & 1;
+  uint32_t key[4], iv[4];  // e-lanes: words 4..7, a-lanes: words 0..3
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    key[i] = pick(R.m, parent[i], parent[4 + i]);
+    iv[i] = pick(R.m, tl::kSha256IV[i], tl::kSha256IV[4 + i]);
+  }
+  uint32_t at = 0, tiles = 0;  // place in the current tile, tiles begun
+  uint32_t used = 0;           // keys that wave 2 has taken, as last seen
+  if (!wait_for<false>(s, kTileReady, 1)) return;
+  for (uint64_t k = 0; k < r.n; ++k) {
+    const uint32_t nb = k < r.full ? in.key.nb : msg_len(8, r.tail_tok).nb;
+    uint32_t h[4], stop = 0;
+    for (uint32_t c = 0; c < nb; ++c) {
+      if (at == kTileComps) {
+        at = 0;
+        ++tiles;
+        if (lane == 0) lds_put(&s.ctl[kTileDone], tiles);
+        if (!wait_for<false>(s, kTileReady, tiles + 1)) return;
+      }
+      const uint32_t* row = &s.tile[tiles & 1][at * kRowWords];
+      ++at;
+      uint32_t p[8], q[8];
+      if (c == 0) {
+        get8(q, row + 8);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          h[i] = R.v[i] = iv[i];
+          p[i] = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)key[i], 0x124, 0xf, 0xf, false) + tl::kSha256K[i];
+          p[4 + i] = key[i] + tl::kSha256K[4 + i];
+        }
+        R.start(p[0]);
+        R.four(p[1], p[2], p[3], p[4]);
+        R.four(p[5], p[6], p[7], q[0]);
+        // rounds 8..63, eight at a time, while the next eight words are on their way
+#pragma unroll
+        for (int g = 1; g < 8; ++g) {
+          uint32_t(&cur)[8] = g & 1 ? q : p;
+          uint32_t(&nxt)[8] = g & 1 ? p : q;
+          const uint32_t* words = &s.sched[8 * (g - 1)];
+          const uint32_t want = 6 * (uint32_t)k + g;
+          u32x4 ctl;
+          if (g > 2 && g < 7) {  // wave 1 is that far ahead by now
+            ctl = lds_get4(s.ctl);
+            get_sched(nxt, words);
+          }
+          R.four(cur[1], cur[2], cur[3], cur[4]);
+          if (g == 7) {
+            R.four(cur[5], cur[6], cur[7], 0);
+            break;
+          }
+          if (g <= 2) {
+            ctl = lds_get4(s.ctl);
+            get_sched(nxt, words);
+          }
+          R.three(cur[5], cur[6], cur[7]);
+          if (__builtin_expect((int32_t)(scalar(ctl[kSchedSeq]) - want) < 0, 0)) {
+            do {
+              ctl = lds_get4(s.ctl);
+              get_sched(nxt, words);
+              stop = scalar(ctl[kStop]);
+            } while (((int32_t)(scalar(ctl[kSchedSeq]) - want) < 0) & !stop);
+          }
+          if (g == 6) used = scalar(ctl[kKeyUsed]);
+          R.fourth(nxt[0]);
+        }
+        if (stop) return;
+      } else {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) R.v[i] = h[i];
+        get8(p, row);
+        get8(q, row + 8);
+        R.start(p[0]);
+#pragma unroll
+        for (int g = 0; g < 8; ++g) {
+          uint32_t(&cur)[8] = g & 1 ? q : p;
+          uint32_t(&nxt)[8] = g & 1 ? p : q;
+          R.four(cur[1], cur[2], cur[3], cur[4]);
+          R.four(cur[5], cur[6], cur[7], g < 7 ? nxt[0] : 0);
+          if (g < 6) get8(cur, row + 8 * (g + 2));
+        }
+      }
+#pragma unroll
+      for (int i = 0; i < 4; ++i) h[i] += R.v[i];
+    }
+#pragma unroll
+    for (int i = 0; i < 4; ++i) key[i] = h[i];
+    if ((uint32_t)k - used >= kRing && !wait_for<false>(s, kKeyUsed, (uint32_t)k + 1 - kRing)) return;
+    if ((lane & ~4u) == 0) lds_put4(&s.ring[k % kRing][a_lane ? 0 : 4], u32x4{key[0], key[1], key[2], key[3]});
+    if (lane == 0) lds_put(&s.ctl[kKeySeq], (uint32_t)k + 1);
+  }
+}
+
+// Row of 16 lanes rotated by 4: swaps the two kinds of lanes.
+__device__ __forceinline__ uint32_t other_lanes(uint32_t v) {
+  return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x124, 0xf, 0xf, true);
+}
+
+// Wave 1: words 16..63 of every block's first compression, plus the round
+// constants. Words 0..7 are the previous key; the tile row holds words 8..15.
+// It has to stay ahead of wave 0's rounds, so it makes two words at a time:
+// P[i] is word 2i in the e-lanes (lanes 0-3 and 8-11 of a row) and word 2i + 1
+// in the others, Q[i] words 2i - 1 and 2i, and
+//   P[i] = ssig1(P[i-1]) + Q[i-3] + ssig0(Q[i-7]) + P[i-8].
+// That is 13 instructions for two words against 22 one by one.
+__device__ __forceinline__ void seq_schedule(SeqShared& s, const ChainIn& in, const Range& r,
+                                             uint32_t lane) {
+  const uint64_t nb = in.key.nb;
+  const bool odd = lane >> 2 & 1;  // the lanes of the odd words
+  const uint32_t m = odd ? 0xffffffffu : 0;
+  uint32_t K[32];
+#pragma unroll
+  for (int i = 8; i < 32; ++i) K[i] = tl::kSha256K[2 * i] ^ (m & (tl::kSha256K[2 * i] ^ tl::kSha256K[2 * i + 1]));
+  uint64_t q = 0;  // the block's first compression
+  for (uint64_t k = 0; k < r.n; ++k, q += nb) {
+    if (!wait_for<false>(s, kTileReady, (uint32_t)(q / kTileComps) + 1)) return;
+    uint32_t lo[8], hi[8], P[8], Q[8];
+    get8(hi, &s.tile[q / kTileComps & 1][(uint32_t)(q % kTileComps) * kRowWords]);
+#pragma unroll
+    for (int i = 4; i < 8; ++i) P[i] = pick(m, hi[2 * i - 7], hi[2 * i - 8]);
+#pragma unroll
+    for (int i = 5; i < 8; ++i) Q[i] = pick(m, hi[2 * i - 8], hi[2 * i - 9]);
+    uint32_t seq, stop;
+    do {
+      const u32x4 ctl = lds_get4(s.ctl);
+      get8(lo, s.ring[(k - 1) % kRing]);
+      seq = scalar(ctl[kKeySeq]);
+      stop = scalar(ctl[kStop]);
+    } while (((int32_t)(seq - (uint32_t)k) < 0) & !stop);
+    if (stop) return;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) P[i] = pick(m, lo[2 * i + 1], lo[2 * i]);
+#pragma unroll
+    for (int i = 1; i < 4; ++i) Q[i] = pick(m, lo[2 * i], lo[2 * i - 1]);
+    Q[4] = pick(m, hi[0], lo[7]);
+#pragma unroll
+    for (int t = 8; t < 32; t += 4) {
+      u32x4 kw;
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        const int i = t + j;
+        const uint32_t x = ssig1(P[(i + 7) & 7]) + (P[i & 7] + ssig0(Q[(i + 1) & 7]) + Q[(i + 5) & 7]);
+        // Q[i]: word 2i - 1 from the odd lanes' P[i-1], word 2i from the even lanes' P[i]
+        const uint32_t before = other_lanes(P[(i + 7) & 7]), now = other_lanes(x);
+        P[i & 7] = x;
+        Q[i & 7] = pick(m, now, before);
+        kw[j] = x + K[i];
+      }
+      // eight words: the even ones, then the odd ones
+      if ((lane & ~4u) == 0) lds_put4(&s.sched[2 * (t - 8) + (odd ? 4 : 0)], kw);
+      if (lane == 0) lds_put(&s.ctl[kSchedSeq], 6 * (uint32_t)k + (t - 8) / 4 + 1);
+    }
+  }
+}
+
+// Wave 2: keys to memory, lookups, hits. Keys are stored in order and only
+// while every block before them was found (or all_keys), as in seq_walk.
+__device__ __forceinline__ void seq_lookup(SeqShared& s, const Dx& x, bool all_keys, const Range& r, uint8_t* keys,
+                                           uint64_t* handles, uint32_t* hits, uint32_t lane) {
+  const bool lookup = x.mem != nullptr;
+  const uint64_t maxp = lookup ? x.mem[1] : 0;
+  uint64_t n_hit = 0;
+  bool missed = false;
+  for (uint64_t k = 0; k < r.n; ++k) {
+    wait_for<true>(s, kKeySeq, (uint32_t)k + 1);
+    uint32_t h[8];
+    get8(h, s.ring[k % kRing]);
+    uint32_t mine = 0;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) mine = lane == (uint32_t)i ? h[i] : mine;
+    if (lane < 8) ((uint32_t*)(keys + 32 * (r.s0 + k)))[lane] = __builtin_bswap32(mine);
+    if (lane == 0) lds_put(&s.ctl[kKeyUsed], (uint32_t)k + 1);  // after the reads of the ring
+    if (lookup && !missed) {
+      uint64_t kw[4];
+      key_words(kw, h);
+      const uint64_t hv = probe_from(x, kw, maxp, 0);
+      if (hv == kMiss) {
+        missed = true;
+        if (!all_keys) break;
+      } else {
+        if (lane == 0) handles[r.s0 + k] = hv;
+        ++n_hit;
+      }
+    }
+  }
+  if (lane == 0) lds_put(&s.ctl[kStop], 1);
+  if (lookup) {
+    for (uint64_t j = n_hit + lane; j < r.n; j += 64) handles[r.s0 + j] = kMiss;
+  }
+  if (lane == 0) *hits = (uint32_t)(lookup ? n_hit : r.n);
+}
+
+// Wave 3: tiles of 64 compressions ahead of wave 0, one per lane.
+__device__ __forceinline__ void seq_tiles(SeqShared& s, const ChainIn& in, const Range& r, uint32_t lane) {
+  const uint64_t nb = in.key.nb;
+  const uint64_t total = r.full * nb + (r.tail_tok ? msg_len(8, r.tail_tok).nb : 0);
+  for (uint64_t t = 0; t * kTileComps < total; ++t) {
+    if (t >= 2 && !wait_for<true>(s, kTileDone, (uint32_t)t - 1)) return;
+    const uint64_t q = t * kTileComps + lane;
+    if (q < total) {
+      const uint64_t k = q / nb;
+      const uint32_t c = (uint32_t)(q - k * nb), len = block_len(r, k, in.bt);
+      const MsgLen m = len == in.bt ? in.key : msg_len(8, len);
+      const uint32_t* tok = in.tokens + r.t0 + k * in.bt;
+      const uint32_t last = 16 * m.nb - 1;
+      uint32_t w[16], hi[8];
+#pragma unroll
+      for (int i = 0; i < 16; ++i) {
+        const uint32_t g = 16 * c + i, j = g - 8;
+        w[i] = j < len ? __builtin_bswap32(tok[j])
+                       : j == len ? 0x80000000u : g == last ? m.lo : g == last - 1 ? m.hi : 0;
+      }
+      if (c == 0) {
+#pragma unroll
+        for (int i = 0; i < 8; ++i) w[i] = 0;
+      }
+#pragma unroll
+      for (int i = 0; i < 8; ++i) hi[i] = w[8 + i];
+      uint32_t* row = &s.tile[t & 1][lane * kRowWords];
+#pragma unroll
+      for (int i = 0; i < 64; i += 4) {
+        u32x4 kw;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          const int g = i + j;
+          if (g >= 16) w[g & 15] += ssig1(w[(g + 14) & 15]) + w[(g + 9) & 15] + ssig0(w[(g + 1) & 15]);
+          kw[j] = w[g & 15] + tl::kSha256K[g];
+        }
+        *(u32x4*)(row + i) = kw;
+      }
+      if (c == 0) {  // words 8..15 as they are, for wave 1
+        *(u32x4*)(row) = u32x4{hi[0], hi[1], hi[2], hi[3]};
+        *(u32x4*)(row + 4) = u32x4{hi[4], hi[5], hi[6], hi[7]};
+      }
+    }
+    __atomic_signal_fence(__ATOMIC_SEQ_CST);  // the tile is written before it is announced
+    if (lane == 0) lds_put(&s.ctl[kTileReady], (uint32_t)t + 1);
+  }
+}
+
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k_chain_waves(ChainArgs a) {
+  __shared__ __align__(16) SeqShared s;
+  const uint32_t lane = threadIdx.x & 63, wave = scalar(threadIdx.x >> 6), c = blockIdx.x;
+  const Range r = chain_range(a.in, c);
+  uint32_t parent[8];
+  parent_words(parent, a.in, c);
+  if (threadIdx.x == 0) {
+#pragma unroll
+    for (int i = 0; i < 8; ++i) s.ring[kRing - 1][i] = parent[i];  // the key before block 0's
+  }
+  if (threadIdx.x < kCtlWords) s.ctl[threadIdx.x] = 0;
+  __syncthreads();
+  if (wave == 2) {
+    seq_lookup(s, a.x, a.all_keys != 0, r, a.keys, a.handles, &a.hits[c], lane);
+  } else if (wave == 3) {
+    seq_tiles(s, a.in, r, lane);
+  } else if (r.n && wave == 0) {
+    __builtin_amdgcn_s_setprio(3);
+    seq_rounds(s, a.in, r, parent, lane);
+  } else if (r.n) {
+    __builtin_amdgcn_s_setprio(2);
+    seq_schedule(s, a.in, r, lane);
+  }
+}
 
 __global__ __launch_bounds__(64) void k_chain(ChainArgs a) {
   const uint32_t lane = threadIdx.x;
@@ -911,21 +1337,26 @@ int launch_chain(const tl_ctx* ctx, void* stream, size_t n_chains, const tl_chai
   hipStream_t s = (hipStream_t)stream;
   ChainArgs a;
   a.in = chain_in(ctx, n_chains, ch, flags);
-  // one chain per wavefront while chains fit the SIMDs, else share
-  const uint64_t simds = 4ull * (uint64_t)sm_count();
-  uint64_t lanes = (n_chains + simds - 1) / simds;
-  a.lanes = (uint32_t)(lanes < 1 ? 1 : (lanes > 64 ? 64 : lanes));
   a.all_keys = (flags & TL_CHAIN_ALL_KEYS) ? 1 : 0;
   a.x.mem = (uint64_t*)index_mem;
   a.x.mask = index_mem ? capacity - 1 : 0;
   a.keys = d_keys;
   a.handles = d_handles;
   a.hits = d_hits;
-  const uint32_t waves = (uint32_t)((n_chains + a.lanes - 1) / a.lanes);
+  a.lanes = 0;
   (void)hipGetLastError();
-  {
+  // A workgroup per chain while that is the faster way: 2,048 chains of 64
+  // blocks take 0.68 ms against 1.33 ms on lanes, 4,096 (16 per compute unit)
+  // 1.32 against 1.34, 8,192 2.47 against 1.46.
+  if (n_chains <= (uint64_t)TL_CHAIN_WAVES_PER_CU * sm_count()) {
     TimedLaunch t(TL_KERNEL_CHAIN, stream);
-    hipLaunchKernelGGL(k_chain, dim3(waves), dim3(64), 0, s, a);
+    hipLaunchKernelGGL(k_chain_waves, dim3((uint32_t)n_chains), dim3(256), 0, s, a);
+  } else {
+    // chains spread over the SIMDs, up to 64 on a wavefront's lanes
+    const uint64_t simds = 4ull * (uint64_t)sm_count();
+    a.lanes = (uint32_t)std::min<uint64_t>((n_chains + simds - 1) / simds, 64);
+    TimedLaunch t(TL_KERNEL_CHAIN, stream);
+    hipLaunchKernelGGL(k_chain, dim3((uint32_t)((n_chains + a.lanes - 1) / a.lanes)), dim3(64), 0, s, a);
   }
   return launched();
 }

@@ -290,6 +290,46 @@ def test_chain_lookup_equals_the_oracle_walk(capacity, flags):
     assert total_hits > 500  # the walk really reused blocks
 
 
+@pytest.mark.parametrize("page_tokens,ppb", [(5, 1), (16, 1), (24, 1), (16, 30)])
+@pytest.mark.parametrize("many", [False, True])
+def test_sequential_walk_at_the_edges_of_its_tiles(page_tokens, ppb, many):
+    """One, two, three and 31 compressions per block: a workgroup of four
+    wavefronts walks a chain in tiles of 64 compressions with 16 keys between
+    its wavefronts; with thousands of chains a lane walks a chain. Chains end,
+    and have their one block with no stored state, around those edges; keys
+    past the first missing one are written only with TL_CHAIN_ALL_KEYS."""
+    ctx, ns, bt = ctx_bt(page_tokens, ppb)
+    edges = [0, 1, 2, 14, 15, 16, 17, 31, 32, 33, 62, 63, 64, 65]
+    data = [wl.tokens((n + hole) * bt + 3, 50 * n + hole) for n in edges for hole in (0, 1)]
+    holes = [n for n in edges for _ in (0, 1)]
+    data += [wl.tokens(130 * bt + bt - 1, 7000 + h) for h in edges]
+    holes += edges
+    lengths = [d.size for d in data] + [0] * (4200 if many else 0)
+    nk = [-(-L // bt) for L in lengths]
+    ch = Chains(ctx, lengths, 1, bt, slot_counts=nk)
+    ch.tokens = np.concatenate(data)
+    ch.d_tok.copy_(i32(ch.tokens.view(np.int32)))
+    want = [ref.block_keys(ns, d.tobytes(), 4 * bt, tail=True) for d in data]
+    idx = new_index(1 << 14)
+    stored = [k for w, h in zip(want, holes) for i, k in enumerate(w) if i != h]
+    assert (dput(idx, stored, np.arange(len(stored)) + 5) == T.TL_INDEX_STORED).all()
+    handle = {k: i + 5 for i, k in enumerate(stored)}
+    for flags in (T.TL_CHAIN_TAIL, T.TL_CHAIN_TAIL | T.TL_CHAIN_ALL_KEYS):
+        log("sequential walk: block tokens", bt, "chains", ch.n, "flags", flags)
+        keys, handles, hits = ch.lookup(ctx, idx, flags)
+        for c, (w, h) in enumerate(zip(want, holes)):
+            s0, n = int(ch.slot_off[c]), min(h, len(w))
+            assert hits[c] == n, (c, h)
+            kept = len(w) if flags & T.TL_CHAIN_ALL_KEYS else min(n + 1, len(w))
+            assert [keys[s0 + i].tobytes() for i in range(kept)] == w[:kept], (c, h)
+            assert (keys[s0 + kept:s0 + len(w)] == SENT).all(), (c, h)
+            assert handles[s0:s0 + len(w)].tolist() == [handle[k] for k in w[:n]] + [T.MISS] * (len(w) - n)
+    keys, _, hits = ch.lookup(ctx, None, T.TL_CHAIN_TAIL)
+    for c, w in enumerate(want):
+        s0 = int(ch.slot_off[c])
+        assert hits[c] == len(w) and [keys[s0 + i].tobytes() for i in range(len(w))] == w, c
+
+
 def test_stage_builds_load_inputs():
     # two layer groups and two pages per block: tables are [2][slots * 2]
     ctx, ns, bt = ctx_bt(16, ppb=2, n_layers=2, groups=[0, 1])
