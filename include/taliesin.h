@@ -435,9 +435,8 @@ int tl_block_fingerprints(const tl_ctx* ctx, void* stream, size_t n, const uint3
  * block after another. A stale or incomplete token index costs time, never
  * correctness. Other key slots of a chain's range hold unspecified bytes.
  * Positions are d_first_block[c] + k, as in tl_chain_stage. A chain is
- * walked in tiles of 1,024 blocks: with few, long chains (at least two tiles'
- * worth of slots, at most 16 (chain, tile) pairs per compute unit, fewer than
- * 2^29 slots) every tile runs on a workgroup of its own, otherwise one
+ * walked in tiles of 63 blocks: up to 8 chains per compute unit (and with
+ * fewer than 2^29 slots) tiles run on wavefronts of their own, otherwise one
  * workgroup walks each chain; d_hits serves as scratch until the call
  * completes. Fewer than 2^24 chains. */
 int tl_chain_lookup_par(const tl_ctx* ctx, void* stream, size_t n_chains, const tl_chains* chains,

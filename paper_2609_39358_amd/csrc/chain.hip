@@ -106,18 +106,19 @@ __device__ __forceinline__ void sha_tokens(uint32_t (&out)[8], const uint32_t (&
   for (int i = 0; i < 8; ++i) st[i] = tl::kSha256IV[i];
   const uint32_t last = 16 * nb - 1;
   for (uint32_t c = 0; c < nb; ++c) {
+    // all sixteen loads go out before the first is needed (an index past the
+    // tokens reads the last one), so a compression waits for memory once
     uint32_t w[16];
+#pragma unroll
+    for (int t = 0; t < 16; ++t) w[t] = tok[min(16 * c + t - PW, bt - 1)];
 #pragma unroll
     for (int t = 0; t < 16; ++t) {
       const uint32_t g = 16 * c + t;  // word index in the message
       const uint32_t j = g - PW;      // token index (wraps for g < PW)
-      uint32_t v;
+      uint32_t v = j < bt ? __builtin_bswap32(w[t]) : j == bt ? 0x80000000u : 0;
       if (t < PW && g < PW) v = pre[t < PW ? t : 0];
-      else if (j < bt) v = __builtin_bswap32(tok[j]);
-      else if (j == bt) v = 0x80000000u;
-      else if (g == last) v = len_lo;
-      else if (g == last - 1) v = len_hi;
-      else v = 0;
+      if (t == 14 && g == last - 1) v = len_hi;
+      if (t == 15 && g == last) v = len_lo;
       w[t] = v;
     }
     compress(st, w);
@@ -253,11 +254,11 @@ __device__ __forceinline__ uint64_t probe_from(const Dx& x, const uint64_t (&k)[
   const uint64_t tag = tag_of(k);
   const uint64_t home = k[1] & x.mask;
   for (uint64_t d = d0; d <= maxp; ++d) {
+    // the slot's words in one request (it is one 64-byte line)
     const uint64_t* slot = slot_ptr(x, (home + d) & x.mask);
-    const uint64_t t = slot[0];
+    const uint64_t t = slot[0], hv = slot[2], k0 = slot[4], k1 = slot[5], k2 = slot[6], k3 = slot[7];
     if (t == 0) return kMiss;
-    if (t == tag && slot[4] == k[0] && slot[5] == k[1] && slot[6] == k[2] && slot[7] == k[3])
-      return slot[2];
+    if (t == tag && k0 == k[0] && k1 == k[1] && k2 == k[2] && k3 == k[3]) return hv;
   }
   return kMiss;
 }
@@ -778,9 +779,11 @@ __device__ __forceinline__ void seq_tiles(SeqShared& s, const ChainIn& in, const
       const uint32_t last = 16 * m.nb - 1;
       uint32_t w[16], hi[8];
 #pragma unroll
+      for (int i = 0; i < 16; ++i) w[i] = tok[min(16 * c + i - 8, len - 1)];
+#pragma unroll
       for (int i = 0; i < 16; ++i) {
         const uint32_t g = 16 * c + i, j = g - 8;
-        w[i] = j < len ? __builtin_bswap32(tok[j])
+        w[i] = j < len ? __builtin_bswap32(w[i])
                        : j == len ? 0x80000000u : g == last ? m.lo : g == last - 1 ? m.hi : 0;
       }
       if (c == 0) {
@@ -897,246 +900,182 @@ struct ParArgs {
   uint32_t* hits;
 };
 
-// One workgroup per chain, kParThreads blocks per tile (1024 while chains
-// are few enough to leave CUs idle, else 256). For block k the
-// token index proposes cand_k, the key a stored block with the same tokens at
-// the same position has; every block then computes c_k = SHA-256(cand_{k-1} |
-// tokens_k) (cand_{-1} = the chain's parent) and looks c_k up in the key
-// index, all independently. If cand_j = c_j for every j < k, induction from
-// c_0 (computed from the true parent) makes c_0..c_k the true chain keys, so
-// the walk is exact up to the first block m where c_m is not in the index
-// (reuse ends at m) or cand_m != c_m (c_m is true and a hit, but c_{m+1} is
-// not known: the chain goes on sequentially from m+1). Results equal the
-// sequential walk's; candidates only decide how much of it runs in parallel.
-template <uint32_t kParThreads>
-__global__ __launch_bounds__(kParThreads) void k_chain_par(ParArgs a) {
-  __shared__ uint32_t cand[kParThreads + 1][8];  // [0]: candidate of the block before the tile
-  __shared__ uint32_t has[kParThreads + 1];
-  __shared__ uint32_t first;  // (thread << 2) | flag of the tile's first flagged block
-  __shared__ uint64_t seq_hits;
+// The parallel walk. For block k the token index proposes cand_k, the key a
+// stored block with the same tokens at the same position has; every block then
+// computes c_k = SHA-256(cand_{k-1} | tokens_k) (cand_{-1} = the chain's
+// parent) and looks c_k up in the key index, all independently. If cand_j =
+// c_j for every j < k, induction from c_0 (computed from the true parent)
+// makes c_0..c_k the true chain keys, so the walk is exact up to the first
+// block m where c_m is not in the index (flag 1: reuse ends at m) or cand_m !=
+// c_m (flag 2: c_m is true and a hit, but c_{m+1} is not known: the chain goes
+// on sequentially from m+1). Results equal the sequential walk's; candidates
+// only decide how much of it runs in parallel.
+//
+// A tile is kTileBlocks blocks of one chain on one wavefront: lane 0 makes the
+// candidate of the block before the tile (in step with the others' own), lanes
+// 1.. are the tile's blocks. What bounds a tile is the instruction count of
+// its four SHA-256 compressions on one lane (about 1,400 each, 1.86 ns per
+// instruction for a wavefront that has its SIMD to itself), so a call's tiles
+// go to as many SIMDs as there are: the corpus's one chain of 6,062 blocks is
+// 97 tiles and takes 25 us (87 us as six tiles of 1,024 blocks, each on one
+// compute unit). A compression's token loads go out together, a slot of an
+// index is one request (28.7 us with loads and compares one after another).
+constexpr uint32_t kTileBlocks = 63;
+
+struct TileShared {
+  uint32_t cand[64][8];  // candidate of the block before the tile, then the tile's blocks'
+  uint32_t has[64];
+};
+
+// LDS written by a wavefront is seen by its own later reads.
+__device__ __forceinline__ void wave_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// Walks blocks [t0, t0 + kTileBlocks) of chain c; returns the tile's first
+// flagged block as (block << 2 | flag), or all ones. One wavefront, whose s is.
+__device__ uint64_t walk_tile(TileShared& s, const ParArgs& a, const Range& r, uint32_t c, uint64_t t0, uint64_t maxp,
+                              uint64_t tmaxp) {
+  const uint32_t lane = threadIdx.x & 63;
+  const uint64_t k = t0 + lane - 1;  // lane 0 of the first tile: the parent
+  const bool live = k < r.n;
+  const uint32_t* tok = a.in.tokens + r.t0 + k * a.in.bt;
+  const uint32_t len = block_len(r, k, a.in.bt);
+  uint32_t cand[8], hc = 0;
+  if (live) {
+    uint32_t f[8];
+    fingerprint(f, a.in, (a.in.first_block ? a.in.first_block[c] : 0) + k, tok, len);
+    uint64_t fw[4];
+    key_words(fw, f);
+    const uint64_t h = probe_from(a.t, fw, tmaxp, 0);
+    if (h < a.n_handles) {
+      const uint32_t* hk = (const uint32_t*)(a.hkeys + 32 * h);
+#pragma unroll
+      for (int i = 0; i < 8; ++i) cand[i] = __builtin_bswap32(hk[i]);
+      hc = 1;
+    }
+  }
+  if (t0 == 0 && lane == 0) {
+    parent_words(cand, a.in, c);
+    hc = 1;
+  }
+  wave_sync();  // the last tile's reads come first
+  if (hc) {
+#pragma unroll
+    for (int i = 0; i < 8; ++i) s.cand[lane][i] = cand[i];
+  }
+  s.has[lane] = hc;
+  wave_sync();
+  uint32_t flag = 0;
+  if (live && lane && s.has[lane - 1]) {
+    uint32_t prev[8], ck[8];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) prev[i] = s.cand[lane - 1][i];
+    chain_key(ck, a.in, prev, tok, len);
+    store_key(a.keys, r.s0 + k, ck);
+    uint64_t kw[4];
+    key_words(kw, ck);
+    const uint64_t hv = probe_from(a.x, kw, maxp, 0);
+    a.handles[r.s0 + k] = hv;
+    bool same = hc != 0;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) same = same && cand[i] == ck[i];
+    flag = hv == kMiss ? 1u : (same ? 0u : 2u);
+  }
+  // (a block without a candidate for its predecessor is never the first
+  // flagged one: that predecessor is flagged, in this tile or before)
+  const uint64_t any = __ballot(flag != 0);
+  if (!any) return ~0ull;
+  const int at = __builtin_ctzll(any);
+  return (t0 + at - 1) << 2 | (uint32_t)__builtin_amdgcn_readlane((int)flag, at);
+}
+
+// Hits of a chain whose first flagged block is known; for a disagreement at
+// block m the chain goes on sequentially from m + 1, after the key that the
+// walk stored for m. Handles past the last hit become misses.
+template <uint32_t kThreads>
+__device__ void finish_chain(const ParArgs& a, const Range& r, uint32_t c, uint64_t first, uint64_t* seq_hits) {
   const uint32_t tid = threadIdx.x;
+  const uint64_t stop = first >> 2;
+  uint64_t n_hit = first == ~0ull ? r.n : stop;
+  if (first != ~0ull && (first & 3) == 2) {
+    if (tid == 0) {
+      const uint32_t* sk = (const uint32_t*)(a.keys + 32 * (r.s0 + stop));
+      uint32_t cur[8];
+#pragma unroll
+      for (int i = 0; i < 8; ++i) cur[i] = __builtin_bswap32(sk[i]);
+      *seq_hits = stop + 1 + seq_walk(a.in, a.x, false, r, stop + 1, cur, a.keys, a.handles);
+    }
+    __syncthreads();
+    n_hit = *seq_hits;
+  }
+  for (uint64_t j = n_hit + tid; j < r.n; j += kThreads) a.handles[r.s0 + j] = kMiss;
+  __syncthreads();  // every thread has read what it needs of hits[c] and *seq_hits
+  if (tid == 0) a.hits[c] = (uint32_t)n_hit;
+}
+
+// A workgroup walks whole chains, a tile per wavefront at a time.
+constexpr uint32_t kParWaves = 4;
+
+__global__ __launch_bounds__(64 * kParWaves) void k_chain_par(ParArgs a) {
+  __shared__ TileShared s[kParWaves];
+  __shared__ uint64_t flagged[kParWaves];
+  __shared__ uint64_t seq_hits;
+  const uint32_t wave = scalar(threadIdx.x >> 6);
   const uint64_t maxp = a.x.mem[1], tmaxp = a.t.mem[1];
   for (uint32_t c = blockIdx.x; c < a.in.n_chains; c += gridDim.x) {
     const Range r = chain_range(a.in, c);
-    const uint64_t pos0 = a.in.first_block ? a.in.first_block[c] : 0;
-    uint64_t stop = r.n;
-    uint32_t kind = 0;
-    if (tid == 0) {
-      uint32_t p[8];
-      parent_words(p, a.in, c);
-#pragma unroll
-      for (int i = 0; i < 8; ++i) cand[0][i] = p[i];
-      has[0] = 1;
-    }
-    for (uint64_t t0 = 0; t0 < r.n; t0 += kParThreads) {
-      const uint64_t k = t0 + tid;
-      const bool live = k < r.n;
-      const uint32_t* tok = a.in.tokens + r.t0 + k * a.in.bt;
-      const uint32_t len = block_len(r, k, a.in.bt);
-      if (tid == 0) first = 0xffffffffu;
-      uint32_t hc = 0;
-      if (live) {
-        uint32_t f[8];
-        fingerprint(f, a.in, pos0 + k, tok, len);
-        uint64_t fw[4];
-        key_words(fw, f);
-        const uint64_t h = probe_from(a.t, fw, tmaxp, 0);
-        if (h < a.n_handles) {
-          const uint32_t* hk = (const uint32_t*)(a.hkeys + 32 * h);
-#pragma unroll
-          for (int i = 0; i < 8; ++i) cand[tid + 1][i] = __builtin_bswap32(hk[i]);
-          hc = 1;
-        }
-      }
-      has[tid + 1] = hc;
+    uint64_t first = ~0ull;
+    for (uint64_t base = 0; base < r.n && first == ~0ull; base += kParWaves * kTileBlocks) {
+      const uint64_t t0 = base + wave * kTileBlocks;
+      const uint64_t f = t0 < r.n ? walk_tile(s[wave], a, r, c, t0, maxp, tmaxp) : ~0ull;
+      if ((threadIdx.x & 63) == 0) flagged[wave] = f;
+      __threadfence_block();  // thread 0 may read a key that another thread stored
       __syncthreads();
-      if (live && has[tid]) {
-        uint32_t prev[8], ck[8];
 #pragma unroll
-        for (int i = 0; i < 8; ++i) prev[i] = cand[tid][i];
-        chain_key(ck, a.in, prev, tok, len);
-        store_key(a.keys, r.s0 + k, ck);
-        uint64_t kw[4];
-        key_words(kw, ck);
-        const uint64_t hv = probe_from(a.x, kw, maxp, 0);
-        a.handles[r.s0 + k] = hv;
-        bool same = hc != 0;
-#pragma unroll
-        for (int i = 0; i < 8; ++i) same = same && cand[tid + 1][i] == ck[i];
-        const uint32_t flag = hv == kMiss ? 1u : (same ? 0u : 2u);
-        if (flag) atomicMin(&first, tid << 2 | flag);
-      }
-      // (a block without a candidate for its predecessor is never the first
-      // flagged one: that predecessor is flagged, in this tile or before)
-      __syncthreads();
-      const uint32_t f = first;
-      if (f != 0xffffffffu) {
-        stop = t0 + (f >> 2);
-        kind = f & 3;
-      }
-      if (stop != r.n) break;  // uniform: every thread read the same `first`
-      __syncthreads();
-      if (tid == 0) {
-#pragma unroll
-        for (int i = 0; i < 8; ++i) cand[0][i] = cand[kParThreads][i];
-        has[0] = has[kParThreads];
-      }
+      for (uint32_t w = 0; w < kParWaves; ++w) first = min(first, flagged[w]);
       __syncthreads();
     }
-    uint64_t n_hit = kind == 1 ? stop : r.n;
-    if (kind == 2) {
-      // block stop is a hit with a true key, but its candidate differs:
-      // continue the chain sequentially from stop + 1
-      if (tid == 0) {
-        const uint32_t l = (uint32_t)(stop % kParThreads);
-        uint32_t prev[8], cur[8];
-#pragma unroll
-        for (int i = 0; i < 8; ++i) prev[i] = cand[l][i];
-        chain_key(cur, a.in, prev, a.in.tokens + r.t0 + stop * a.in.bt, block_len(r, stop, a.in.bt));
-        seq_hits = stop + 1 + seq_walk(a.in, a.x, false, r, stop + 1, cur, a.keys, a.handles);
-      }
-      __syncthreads();
-      n_hit = seq_hits;
-    }
-    for (uint64_t j = n_hit + tid; j < r.n; j += kParThreads) a.handles[r.s0 + j] = kMiss;
-    if (tid == 0) a.hits[c] = (uint32_t)n_hit;
-    __syncthreads();  // LDS is reused by the next chain
+    finish_chain<64 * kParWaves>(a, r, c, first, &seq_hits);
   }
 }
 
-// The same walk with the tiles of a chain spread over workgroups, for a few
-// long chains (one workgroup per chain would walk their tiles one after
-// another). Pass 1 runs one workgroup per (chain, tile): the candidate of the
-// block before the tile comes from the token index like every other
-// candidate, the tile's blocks are hashed, probed and compared as above, and
-// the tile's first flagged block k goes to hits[c] as min(k << 2 | flag)
-// (k_par_init sets every hits[c] to all ones first). A tile that starts
-// after a block already flagged is skipped: only the first flag counts.
-// Pass 2 (k_chain_par_finish, one workgroup per chain) turns hits[c] into
-// the hit count: for a disagreement at block m it continues the chain
-// sequentially from m + 1, whose predecessor's key pass 1 stored and is
-// true; it sets the handles after the last hit to misses. Results equal
-// k_chain_par's.
+// The same with a chain's tiles on `spread` wavefronts of their own. Pass 1
+// runs the tiles; a tile's first flagged block k goes to hits[c] as
+// min(k << 2 | flag) (k_par_init sets every hits[c] to all ones first). Tiles
+// after a block already flagged are skipped: only the first flag counts. Pass
+// 2 (k_chain_par_finish, one workgroup per chain) turns hits[c] into the hit
+// count. Results equal k_chain_par's.
 __global__ __launch_bounds__(256) void k_par_init(uint32_t* hits, uint32_t n) {
   for (uint32_t i = blockIdx.x * 256 + threadIdx.x; i < n; i += gridDim.x * 256) hits[i] = 0xffffffffu;
 }
 
-template <uint32_t kParThreads>
-__global__ __launch_bounds__(kParThreads) void k_chain_par_tiles(ParArgs a, uint32_t n_tiles) {
-  __shared__ uint32_t cand[kParThreads + 1][8];  // [0]: candidate of the block before the tile
-  __shared__ uint32_t has[kParThreads + 1];
-  __shared__ uint32_t first;
-  __shared__ uint32_t skip;
-  const uint32_t tid = threadIdx.x;
+__global__ __launch_bounds__(64) void k_chain_par_tiles(ParArgs a, uint32_t spread) {
+  __shared__ TileShared s;
   const uint64_t maxp = a.x.mem[1], tmaxp = a.t.mem[1];
-  const uint64_t pairs = (uint64_t)a.in.n_chains * n_tiles;
-  for (uint64_t q = blockIdx.x; q < pairs; q += gridDim.x) {
-    const uint32_t c = (uint32_t)(q % a.in.n_chains);
-    const uint64_t t0 = (q / a.in.n_chains) * kParThreads;
-    const Range r = chain_range(a.in, c);
-    if (t0 >= r.n) continue;  // uniform: every thread computed the same range
-    const uint64_t pos0 = a.in.first_block ? a.in.first_block[c] : 0;
-    if (tid == 0) {
-      first = 0xffffffffu;
-      const uint32_t seen = __hip_atomic_load(&a.hits[c], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      skip = seen != 0xffffffffu && (uint64_t)(seen >> 2) < t0;
-      uint32_t hc0 = 0;
-      if (!skip) {
-        if (t0 == 0) {
-          uint32_t p[8];
-          parent_words(p, a.in, c);
-#pragma unroll
-          for (int i = 0; i < 8; ++i) cand[0][i] = p[i];
-          hc0 = 1;
-        } else {
-          const uint64_t k = t0 - 1;
-          uint32_t f[8];
-          fingerprint(f, a.in, pos0 + k, a.in.tokens + r.t0 + k * a.in.bt, block_len(r, k, a.in.bt));
-          uint64_t fw[4];
-          key_words(fw, f);
-          const uint64_t h = probe_from(a.t, fw, tmaxp, 0);
-          if (h < a.n_handles) {
-            const uint32_t* hk = (const uint32_t*)(a.hkeys + 32 * h);
-#pragma unroll
-            for (int i = 0; i < 8; ++i) cand[0][i] = __builtin_bswap32(hk[i]);
-            hc0 = 1;
-          }
-        }
-      }
-      has[0] = hc0;
+  const uint32_t c = blockIdx.x % a.in.n_chains;
+  const Range r = chain_range(a.in, c);
+  const uint64_t t_first = (uint64_t)(blockIdx.x / a.in.n_chains) * kTileBlocks;
+  for (uint64_t t0 = t_first; t0 < r.n; t0 += (uint64_t)spread * kTileBlocks) {
+    if (t0 != t_first) {  // (the first tiles all start at the same time)
+      const uint32_t seen = scalar(__hip_atomic_load(&a.hits[c], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+      if (seen != 0xffffffffu && (seen >> 2) < t0) return;
     }
-    __syncthreads();
-    if (skip) {
-      __syncthreads();  // nobody reads this tile's LDS any more
-      continue;
+    const uint64_t first = walk_tile(s, a, r, c, t0, maxp, tmaxp);
+    if (first != ~0ull) {
+      if (threadIdx.x == 0) atomicMin(&a.hits[c], (uint32_t)first);
+      return;
     }
-    const uint64_t k = t0 + tid;
-    const bool live = k < r.n;
-    const uint32_t* tok = a.in.tokens + r.t0 + k * a.in.bt;
-    const uint32_t len = block_len(r, k, a.in.bt);
-    uint32_t hc = 0;
-    if (live) {
-      uint32_t f[8];
-      fingerprint(f, a.in, pos0 + k, tok, len);
-      uint64_t fw[4];
-      key_words(fw, f);
-      const uint64_t h = probe_from(a.t, fw, tmaxp, 0);
-      if (h < a.n_handles) {
-        const uint32_t* hk = (const uint32_t*)(a.hkeys + 32 * h);
-#pragma unroll
-        for (int i = 0; i < 8; ++i) cand[tid + 1][i] = __builtin_bswap32(hk[i]);
-        hc = 1;
-      }
-    }
-    has[tid + 1] = hc;
-    __syncthreads();
-    if (live && has[tid]) {
-      uint32_t prev[8], ck[8];
-#pragma unroll
-      for (int i = 0; i < 8; ++i) prev[i] = cand[tid][i];
-      chain_key(ck, a.in, prev, tok, len);
-      store_key(a.keys, r.s0 + k, ck);
-      uint64_t kw[4];
-      key_words(kw, ck);
-      const uint64_t hv = probe_from(a.x, kw, maxp, 0);
-      a.handles[r.s0 + k] = hv;
-      bool same = hc != 0;
-#pragma unroll
-      for (int i = 0; i < 8; ++i) same = same && cand[tid + 1][i] == ck[i];
-      const uint32_t flag = hv == kMiss ? 1u : (same ? 0u : 2u);
-      if (flag) atomicMin(&first, tid << 2 | flag);
-    }
-    __syncthreads();
-    if (tid == 0 && first != 0xffffffffu)
-      atomicMin(&a.hits[c], (uint32_t)((t0 + (first >> 2)) << 2) | (first & 3));
-    __syncthreads();  // LDS is reused by the next tile
   }
 }
 
 __global__ __launch_bounds__(256) void k_chain_par_finish(ParArgs a) {
   __shared__ uint64_t seq_hits;
-  const uint32_t tid = threadIdx.x;
   for (uint32_t c = blockIdx.x; c < a.in.n_chains; c += gridDim.x) {
-    const Range r = chain_range(a.in, c);
     const uint32_t f = a.hits[c];  // final: pass 1 has completed
-    const uint64_t stop = f == 0xffffffffu ? r.n : (uint64_t)(f >> 2);
-    const uint32_t kind = f == 0xffffffffu ? 0u : (f & 3);
-    uint64_t n_hit = kind == 1 ? stop : r.n;
-    if (kind == 2) {
-      // block stop is a hit with a true key, but its candidate differs
-      if (tid == 0) {
-        const uint32_t* sk = (const uint32_t*)(a.keys + 32 * (r.s0 + stop));
-        uint32_t cur[8];
-#pragma unroll
-        for (int i = 0; i < 8; ++i) cur[i] = __builtin_bswap32(sk[i]);
-        seq_hits = stop + 1 + seq_walk(a.in, a.x, false, r, stop + 1, cur, a.keys, a.handles);
-      }
-      __syncthreads();
-      n_hit = seq_hits;
-    }
-    for (uint64_t j = n_hit + tid; j < r.n; j += 256) a.handles[r.s0 + j] = kMiss;
-    __syncthreads();  // every thread has read hits[c]
-    if (tid == 0) a.hits[c] = (uint32_t)n_hit;
+    finish_chain<256>(a, chain_range(a.in, c), c, f == 0xffffffffu ? ~0ull : f, &seq_hits);
     __syncthreads();
   }
 }
@@ -1378,25 +1317,23 @@ int launch_chain_par(const tl_ctx* ctx, void* stream, size_t n_chains, const tl_
   a.handles = d_handles;
   a.hits = d_hits;
   (void)hipGetLastError();
-  // Tiles of 1024 blocks per chain, at most: a chain's blocks never exceed the
-  // call's slots. With at least two of them per chain and few (chain, tile)
-  // pairs, the tiles of each chain go to workgroups of their own.
-  const uint64_t tiles = (ch->n_slots + 1023) / 1024;
-  const int cus = sm_count();
-  const bool spread = tiles >= 2 && (uint64_t)n_chains * tiles <= (uint64_t)cus * 16 &&
-                      ch->n_slots < (1ull << 29);
+  // A chain's blocks never exceed the call's slots. Its tiles go to wavefronts
+  // of their own while that keeps the call at 16 wavefronts per compute unit
+  // (measured: 25 us for one chain of 6,062 blocks, 42 us for 256 of 400);
+  // past that, and where the workgroup of one chain holds all its tiles (one
+  // launch instead of three), a workgroup walks a whole chain. hits[c] holds
+  // a flagged block in 30 bits.
+  const uint64_t tiles = (ch->n_slots + kTileBlocks - 1) / kTileBlocks;
+  const uint64_t spread = std::min<uint64_t>(tiles, 16 * (uint64_t)sm_count() / n_chains);
   {
     TimedLaunch t(TL_KERNEL_CHAIN, stream);
-    if (spread) {
+    if (tiles > kParWaves && spread >= 2 && ch->n_slots < (1ull << 29)) {
       hipLaunchKernelGGL(k_par_init, dim3(grid_for(n_chains, 256, 4096)), dim3(256), 0, s, d_hits,
                          (uint32_t)n_chains);
-      hipLaunchKernelGGL(k_chain_par_tiles<1024>, dim3((uint32_t)(n_chains * tiles)), dim3(1024), 0, s, a,
-                         (uint32_t)tiles);
+      hipLaunchKernelGGL(k_chain_par_tiles, dim3((uint32_t)(n_chains * spread)), dim3(64), 0, s, a, (uint32_t)spread);
       hipLaunchKernelGGL(k_chain_par_finish, dim3(grid_for(n_chains, 1, 1u << 16)), dim3(256), 0, s, a);
     } else {
-      const dim3 grid(grid_for(n_chains, 1, 1u << 16));
-      if (n_chains <= (size_t)cus * 4) hipLaunchKernelGGL(k_chain_par<1024>, grid, dim3(1024), 0, s, a);
-      else hipLaunchKernelGGL(k_chain_par<256>, grid, dim3(256), 0, s, a);
+      hipLaunchKernelGGL(k_chain_par, dim3(grid_for(n_chains, 1, 1u << 16)), dim3(64 * kParWaves), 0, s, a);
     }
   }
   return launched();

@@ -674,6 +674,29 @@ def test_parallel_walk_one_long_chain(case):
     assert hitsp[0] == want and np.array_equal(hp[:ch.n_slots], handles[:ch.n_slots])
 
 
+@pytest.mark.parametrize("hole", [None, 0, 61, 62, 63, 125, 126, 188, 189, 251, 252, 253])
+def test_parallel_walk_at_the_edges_of_its_tiles(hole):
+    """Tiles are 63 blocks on a wavefront, four of them on the workgroup of a
+    chain: chains that end around those edges, and a block there with no token
+    index entry, with no key, or stored after another prefix (its successors'
+    candidates are another document's keys)."""
+    ctx, ns, bt = ctx_bt(16)
+    docs, _ = stored_docs(ns, bt, 3, 260, 140)
+    kw = {}
+    if hole is not None:
+        dec = docs[2].copy()
+        dec[hole * bt] ^= 1
+        kw = {"token_skip": {hole}, "skip": {260 + hole}, "decoys": [dec]}
+    two = TwoIndexes(ctx, ns, bt, docs, cap=4096, **kw)
+    reqs = [d[:n * bt + 1] for d in docs for n in (0, 1, 62, 63, 64, 126, 127, 189, 252, 253, 259)]
+    ch = Chains(ctx, [r.size for r in reqs], 0, bt)
+    ch.tokens[:] = np.concatenate(reqs)
+    ch.d_tok.copy_(i32(ch.tokens.view(np.int32)))
+    for c in (ch, pad_chains(ctx, ch, bt, 4100)):
+        keys, handles, hits = par_lookup(ctx, c, two)
+        check_walk(c, ns, bt, two.index, keys, handles, hits)
+
+
 def test_parallel_walk_with_parents_and_positions():
     ctx, ns, bt = ctx_bt(16)
     rng = np.random.default_rng(3)
