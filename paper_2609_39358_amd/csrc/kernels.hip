@@ -13,7 +13,9 @@
 // summed with a ds_swizzle butterfly.
 //
 //   save:  k_save_seg  (page -> record payload, chunk digest -> table)
-//          k_save_meta (header, token ids, padding, root over the metadata)
+//          k_save_meta (header, token ids, padding, root over the metadata;
+//                       long digest tables are hashed beside the copy, see
+//                       k_save_slice)
 //   load:  k_load_init (clear the per-block status words)
 //          k_load_main (one grid: per block, pointer/length/root/header/
 //                       position/key/token checks; per chunk, record -> page
@@ -27,6 +29,7 @@
 // specification); the tree arrangement is this library's record format.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <mutex>
 #include <vector>
 
@@ -228,7 +231,8 @@ struct SegArgs {
   uint32_t n;            // blocks
   uint32_t t_begin;      // first chunk index of the range handled (save by layers)
   uint32_t n_sub;        // chunks per block in that range
-  uint32_t total;        // n * n_sub work items
+  uint32_t first;        // work items [first, total) (first is 0 but for a slice of a save)
+  uint32_t total;        // n * n_sub work items (a slice: its end)
   uint32_t order;        // work order (0, 1 or 2, as TL_SAVE_ORDER / TL_LOAD_ORDER)
   uint32_t disabled;     // load checks switched off (sabotage build only; else 0)
   uint32_t* status;      // load: per-block status words
@@ -447,13 +451,14 @@ __device__ uint64_t zero_hash(char* dst, uint32_t rows, uint32_t lane) {
   return c.finish(lane, rows, z);
 }
 
-// The chunk loop of the save, for both save kernels: one wavefront per
-// (block, chunk) work item, striding over the grid.
+// The chunk loop of the save, for all save kernels: one wavefront per
+// (block, chunk) work item, striding over `wgs` workgroups of which this is
+// the wg-th.
 template <int B, int PF>
-__device__ __forceinline__ void save_chunks(const SegArgs& a) {
+__device__ __forceinline__ void save_chunks(const SegArgs& a, uint32_t wg, uint32_t wgs) {
   const uint32_t lane = threadIdx.x & 63;
-  const uint32_t step = gridDim.x * kSegWaves;
-  for (uint32_t w = blockIdx.x * kSegWaves + uniform(threadIdx.x >> 6); w < a.total; w += step) {
+  const uint32_t step = wgs * kSegWaves;
+  for (uint32_t w = a.first + wg * kSegWaves + uniform(threadIdx.x >> 6); w < a.total; w += step) {
     const Item it = decode(a, w);
     const uint64_t rec = a.rec[it.b];
     if (rec == 0 || (rec & 15)) continue;
@@ -474,7 +479,7 @@ __device__ __forceinline__ void save_chunks(const SegArgs& a) {
 // The whole device to itself: a whole 64 KiB chunk in flight per wavefront,
 // one wavefront per SIMD (about 300 registers per lane).
 __global__ __launch_bounds__(64 * kSegWaves) void k_save_seg(SegArgs a) {
-  save_chunks<TL_SAVE_BATCH_ROWS, TL_SAVE_PREFETCH>(a);
+  save_chunks<TL_SAVE_BATCH_ROWS, TL_SAVE_PREFETCH>(a, blockIdx.x, gridDim.x);
 }
 
 // Beside other kernels (tl_save_layers' default): half the chunk per batch
@@ -486,7 +491,7 @@ __global__ __launch_bounds__(64 * kSegWaves) void k_save_seg(SegArgs a) {
 // overlap where k_save_seg's fall behind them.
 __global__ __launch_bounds__(64 * kSegWaves) __attribute__((amdgpu_waves_per_eu(2))) void
 k_save_seg_shared(SegArgs a) {
-  save_chunks<TL_SHARED_SAVE_BATCH_ROWS, 0>(a);
+  save_chunks<TL_SHARED_SAVE_BATCH_ROWS, 0>(a, blockIdx.x, gridDim.x);
 }
 
 // Root checksum over one metadata tile already staged in LDS: lane k (k < 4)
@@ -565,9 +570,61 @@ __device__ __forceinline__ uint32_t meta_word(const MetaArgs& a, const MetaWords
 // over the previous tile meanwhile (two LDS buffers). The 16 bytes holding
 // the root are written last.
 constexpr uint32_t kMetaThreads = kMetaTile / 16;
+typedef uint64_t MetaTiles[2][kMetaTile / 8];
 
-__global__ __launch_bounds__(kMetaThreads) void k_save_meta(MetaArgs a) {
-  __shared__ uint64_t tile[2][kMetaTile / 8];
+__device__ __forceinline__ MetaWords meta_words(const MetaArgs& a, uint32_t b, uint32_t tk) {
+  MetaWords m;
+  m.tail = tk < a.g.block_tokens ? tk : 0;
+  m.key32 = (const uint32_t*)(a.keys + 32ull * b);
+  m.tok = a.tokens + (uint64_t)a.g.block_tokens * b;
+  m.bi = a.bidx[b];
+  m.tk = tk;
+  return m;
+}
+
+// Feeds metadata bytes [from, to) (multiples of 32) to the root's accumulators
+// (lanes 0-3 of the first wavefront), writing what the record does not hold
+// yet if `write`.
+__device__ __forceinline__ void meta_hash(const MetaArgs& a, const MetaWords& m, uint64_t rec, uint32_t from, uint32_t to,
+                                          bool write, MetaTiles& tile, uint64_t& acc) {
+  const uint32_t tid = threadIdx.x;
+  auto stage = [&](uint32_t off, uint64_t* buf) {
+    const uint32_t o = off + 16 * tid;
+    if (o >= to) return;
+    v4u x;
+    if (o >= tl::kHeaderBytes && o + 16 <= a.g.tok_off) {
+      x = *(const v4u*)(rec + o);  // chunk digests: already in place
+    } else {
+      x = v4u{meta_word(a, m, rec, o), meta_word(a, m, rec, o + 4), meta_word(a, m, rec, o + 8),
+              meta_word(a, m, rec, o + 12)};
+      if (write && o != tl::kRootOffset) *(v4u*)(rec + o) = x;
+    }
+    // the root field is zero in x (the template holds zeros there)
+    buf[2 * tid] = ((uint64_t)x.y << 32 | x.x) * kP2;
+    buf[2 * tid + 1] = ((uint64_t)x.w << 32 | x.z) * kP2;
+  };
+  stage(from, tile[0]);
+  __syncthreads();
+  for (uint32_t off = from, t = 0; off < to; off += kMetaTile, ++t) {
+    if (off + kMetaTile < to) stage(off + kMetaTile, tile[(t + 1) & 1]);
+    if (tid < 64) hash_tile_premul(tile[t & 1], min(to - off, kMetaTile), tid, acc);
+    __syncthreads();
+  }
+}
+
+// Chunk digests of block b that are in place once work items [0, items) are
+// done, and the metadata bytes that can be hashed then.
+__device__ __forceinline__ uint32_t meta_ready(const MetaArgs& a, uint32_t b, uint32_t items) {
+  const uint64_t before = (uint64_t)b * a.g.n_seg;
+  const uint32_t done = items <= before ? 0 : (uint32_t)min((uint64_t)items - before, (uint64_t)a.g.n_seg);
+  return done ? (tl::kHeaderBytes + 8 * done) & ~31u : 0;
+}
+
+// Finishes the metadata of every block. `hashed`: work items whose digests
+// k_save_slice has already hashed (0: none); the accumulators of a block it has
+// begun are in the record's first 32 bytes.
+__global__ __launch_bounds__(kMetaThreads) void k_save_meta(MetaArgs a, uint32_t hashed) {
+  __shared__ MetaTiles tile;
   const uint32_t tid = threadIdx.x;
   const uint32_t lane = tid & 63;
   const uint32_t b = blockIdx.x;
@@ -586,38 +643,18 @@ __global__ __launch_bounds__(kMetaThreads) void k_save_meta(MetaArgs a) {
     if (tid == 0 && a.out_status) a.out_status[b] = TL_BADARG;
     return;
   }
-  MetaWords m;
-  m.tail = tk < a.g.block_tokens ? tk : 0;
-  m.key32 = (const uint32_t*)(a.keys + 32ull * b);
-  m.tok = a.tokens + (uint64_t)a.g.block_tokens * b;
-  m.bi = a.bidx[b];
-  m.tk = tk;
-  auto stage = [&](uint32_t off, uint64_t* buf) {
-    const uint32_t o = off + 16 * tid;
-    if (o >= meta) return;
-    v4u x;
-    if (o >= tl::kHeaderBytes && o + 16 <= a.g.tok_off) {
-      x = *(const v4u*)(rec + o);  // chunk digests: already in place
-    } else {
-      x = v4u{meta_word(a, m, rec, o), meta_word(a, m, rec, o + 4), meta_word(a, m, rec, o + 8),
-              meta_word(a, m, rec, o + 12)};
-      if (o != tl::kRootOffset) *(v4u*)(rec + o) = x;
-    }
-    // the root field is zero in x (the template holds zeros there)
-    buf[2 * tid] = ((uint64_t)x.y << 32 | x.x) * kP2;
-    buf[2 * tid + 1] = ((uint64_t)x.w << 32 | x.z) * kP2;
-  };
+  const MetaWords m = meta_words(a, b, tk);
+  const uint32_t from = meta_ready(a, b, hashed);
   uint64_t acc = root_init(lane);
-  stage(0, tile[0]);
-  __syncthreads();
-  for (uint32_t off = 0, t = 0; off < meta; off += kMetaTile, ++t) {
-    if (off + kMetaTile < meta) stage(off + kMetaTile, tile[(t + 1) & 1]);
-    if (tid < 64) {
-      const uint32_t nb = meta - off < kMetaTile ? meta - off : kMetaTile;
-      hash_tile_premul(tile[t & 1], nb, lane, acc);
-    }
-    __syncthreads();
+  if (from) {
+    if (tid < 4) acc = *(const uint64_t*)(rec + 8 * tid);
+    __syncthreads();  // the accumulators are read before the header takes their place
+    const uint32_t o = 16 * tid;
+    if (o < tl::kHeaderBytes && o != tl::kRootOffset)
+      *(v4u*)(rec + o) = v4u{meta_word(a, m, rec, o), meta_word(a, m, rec, o + 4), meta_word(a, m, rec, o + 8),
+                             meta_word(a, m, rec, o + 12)};
   }
+  meta_hash(a, m, rec, from, meta, true, tile, acc);
   if (tid < 64) {
     const uint64_t root = finish_root(acc, meta);
     if (tid == 0) {
@@ -627,6 +664,40 @@ __global__ __launch_bounds__(kMetaThreads) void k_save_meta(MetaArgs a) {
       if (a.out_status) a.out_status[b] = TL_ACCEPT;
     }
   }
+}
+
+// A slice of a save whose records have long digest tables: workgroups
+// [0, n_hash) hash the digests that the launches before this one have
+// completed, one block each from block b0 on, while the others copy the work
+// items [s.first, s.total). The root is one serial chain (35 ns per four
+// digests), 0.6 ms for a block of 550 pages; run after the copy it left the
+// device idle for that long (save_cuts says how the slices are sized).
+struct SliceArgs {
+  SegArgs s;
+  MetaArgs m;
+  uint32_t b0, n_hash;
+  uint32_t from_items, to_items;  // digests of work items [from_items, to_items)
+};
+
+__global__ __launch_bounds__(64 * kSegWaves) void k_save_slice(SliceArgs a) {
+  static_assert(kMetaThreads == 64 * kSegWaves, "one workgroup size for both parts");
+  __shared__ MetaTiles tile;
+  if (blockIdx.x >= a.n_hash) {
+    save_chunks<TL_SAVE_BATCH_ROWS, TL_SAVE_PREFETCH>(a.s, blockIdx.x - a.n_hash, gridDim.x - a.n_hash);
+    return;
+  }
+  const uint32_t tid = threadIdx.x, lane = tid & 63;
+  const uint32_t b = a.b0 + blockIdx.x;
+  const uint64_t rec = a.m.rec[b];
+  const uint32_t tk = block_tok(a.m.g, a.m.n_tokens, b);
+  const uint32_t from = meta_ready(a.m, b, a.from_items), to = meta_ready(a.m, b, a.to_items);
+  if (from == to || rec == 0 || (rec & 15) || tk == 0 ||
+      !block_pages_ok(a.m.g, a.m.tables, a.m.n, b, a.m.n_pages, 0, lane, pages_used(a.m.g, tk)))
+    return;
+  uint64_t acc = root_init(lane);
+  if (from && tid < 4) acc = *(const uint64_t*)(rec + 8 * tid);
+  meta_hash(a.m, meta_words(a.m, b, tk), rec, from, to, false, tile, acc);
+  if (tid < 4) *(uint64_t*)(rec + 8 * tid) = acc;
 }
 
 // ---- load ---------------------------------------------------------------------
@@ -801,6 +872,7 @@ void fill_seg(SegArgs& a, const tl_ctx* ctx, size_t n, const uint64_t* rec, cons
   // layers [layer_begin, layer_end) own slabs [2 * begin * ppb, 2 * end * ppb)
   a.t_begin = 2 * layer_begin * ctx->geo.ppb * ctx->geo.cps;
   a.n_sub = 2 * (layer_end - layer_begin) * ctx->geo.ppb * ctx->geo.cps;
+  a.first = 0;
   a.total = (uint32_t)(n * a.n_sub);
   a.order = 0;
   a.disabled = g_disabled_checks;
@@ -930,13 +1002,84 @@ int launch_save_seal(const tl_ctx* ctx, void* stream, size_t n, int64_t n_pages,
   fill_meta(m, ctx, n, d_rec, nullptr, blk, n_pages, nullptr, d_status);
   (void)hipGetLastError();
   timed(TL_KERNEL_SAVE_META, s, [&] {
-    hipLaunchKernelGGL(k_save_meta, dim3((uint32_t)n), dim3(kMetaThreads), 0, s, m);
+    hipLaunchKernelGGL(k_save_meta, dim3((uint32_t)n), dim3(kMetaThreads), 0, s, m, 0u);
+  });
+  return launched();
+}
+
+// Where a save's launches end (work items), if it is worth more than one.
+//
+// The last launch's digests are hashed when nothing is left to copy, so it is
+// short: 2,048 items, 18 us of hashing (8.6 ns per digest). A launch before it
+// is as long as its copy can hide the hashing of what came before: an item of
+// 64 KiB copies in 24 ns at 5.5 TB/s, so each launch may be 2.8 times the next
+// one (twice for small chunks, which hide less than all of it), until a launch
+// can hide a block's whole table. A boundary between launches costs about
+// 6 us, so blocks below 8,192 digests (70 us) keep one launch.
+// One block of 550 pages (66,000 chunks of 64 KiB, four launches): 2,093 us
+// with one launch and all of the hashing after it, 1,574 us so (38 us of that
+// hash the token ids, which come last); three such blocks 4,352 and 3,989 us.
+struct SaveCuts {
+  uint32_t n = 0;
+  uint32_t end[32];
+};
+constexpr uint32_t kSliceMin = 2048;
+
+SaveCuts save_cuts(const Geo& g, size_t n) {
+  SaveCuts c;
+  const uint64_t total = (uint64_t)n * g.n_seg;
+  if (g.n_seg < 4 * kSliceMin) return c;
+  const uint64_t item_bytes = 2 * g.slab_bytes / g.cps;  // copied: read and written
+  uint32_t size[32], k = 0;
+  uint64_t left = total, r = kSliceMin;
+  while (left) {
+    // (at least twice as long each time, and fewer than 2^31 items: at most 22)
+    const bool all = 3 * r >= 2 * left || (k && size[k - 1] >= g.n_seg);
+    size[k] = (uint32_t)(all ? left : r);
+    left -= size[k++];
+    r = std::max(2 * r, r * item_bytes / 47000);
+  }
+  uint32_t at = 0;
+  while (k) c.end[c.n++] = at += size[--k];
+  return c;
+}
+
+// A save in slices: launch i copies items [end[i-1], end[i]) and hashes the
+// digests that launch i-1 completed; k_save_meta hashes the rest.
+int launch_save_sliced(const tl_ctx* ctx, hipStream_t s, size_t n, const tl_cache* src, const tl_blocks* blk,
+                       const uint64_t* d_rec, uint8_t* d_status, const SaveCuts& cuts) {
+  SliceArgs a;
+  fill_seg(a.s, ctx, n, d_rec, blk->d_tables, blk->d_n_tokens, src, nullptr);
+  fill_meta(a.m, ctx, n, d_rec, nullptr, blk, src->n_pages, nullptr, d_status);
+  a.from_items = a.to_items = 0;
+  (void)hipGetLastError();
+  for (uint32_t i = 0; i < cuts.n; ++i) {
+    const uint32_t end = cuts.end[i];
+    a.s.first = a.to_items;
+    a.s.total = end;
+    const uint32_t grid = seg_grid(end - a.s.first);
+    timed(TL_KERNEL_SAVE_SEG, s, [&] {
+      if (a.s.first == 0) {
+        hipLaunchKernelGGL(k_save_seg, dim3(grid), dim3(64 * kSegWaves), 0, s, a.s);
+      } else {
+        a.b0 = a.from_items / a.m.g.n_seg;
+        a.n_hash = (a.to_items - 1) / a.m.g.n_seg - a.b0 + 1;
+        hipLaunchKernelGGL(k_save_slice, dim3(a.n_hash + grid), dim3(64 * kSegWaves), 0, s, a);
+      }
+    });
+    a.from_items = a.to_items;
+    a.to_items = end;
+  }
+  timed(TL_KERNEL_SAVE_META, s, [&] {
+    hipLaunchKernelGGL(k_save_meta, dim3((uint32_t)n), dim3(kMetaThreads), 0, s, a.m, a.from_items);
   });
   return launched();
 }
 
 int launch_save(const tl_ctx* ctx, void* stream, size_t n, const tl_cache* src,
                 const tl_blocks* blk, const uint64_t* d_rec, uint8_t* d_status) {
+  const SaveCuts cuts = save_cuts(ctx->geo, n);
+  if (cuts.n > 1) return launch_save_sliced(ctx, (hipStream_t)stream, n, src, blk, d_rec, d_status, cuts);
   int r = launch_save_layers(ctx, stream, n, src, blk, d_rec, 0, ctx->geo.n_layers, TL_SAVE_EXCLUSIVE);
   if (r) return r;
   return launch_save_seal(ctx, stream, n, src->n_pages, blk, d_rec, d_status);

@@ -82,3 +82,46 @@ def test_edge_geometry_shared_save(name):
         got = store.buf.cpu().numpy()
         for b in range(n):
             assert got[b].tobytes() == recs_o[b], (len(parts), b)
+
+
+# Blocks of 1 KiB slabs with digest tables on both sides of the length from
+# which a save hashes them beside the copy: 8,188 (one launch), 8,192 and 10,000
+# digests; the last case also ends in a partial block and holds a refused block
+# and a missing record, whose digests are never made.
+@pytest.mark.parametrize("layers,ppb,n,odd", [(2, 2047, 1, False), (2, 2048, 1, False), (2, 2048, 3, False),
+                                              (1, 5000, 4, True)])
+def test_long_digest_tables(layers, ppb, n, odd):
+    from paper_2609_39358_amd import taliesin as T
+    from paper_2609_39358_amd.device import RecordStore
+    from tests.gpu_case import i32
+    geom = wl.Geometry(layers, 1, 64, 8, pages_per_block=ppb)
+    c = Case(geom, n, n * ppb + 5, n * ppb + 5, seed=23)
+    c.make_src()
+    counts = np.full(n, geom.block_tokens, np.int32)
+    tables = c.t_src.copy()
+    ptr_on = np.ones(n, bool)
+    if odd:
+        counts[3] = 8 * 3001 + 3  # pages 3,002.. of the last block hold no tokens
+        tables[:, 3 * ppb + 3002:] = -1
+        tables[:, 1 * ppb + 4321] = c.src_pages
+        ptr_on[2] = False
+        c.tokens[3, counts[3]:] = 0
+        c.d_tokens = i32(c.tokens.view(np.int32))
+    hk, hv = host_layers(c.src)
+    recs_o, st_o = ref.save(c.lay, c.ns, hk, hv, tables, [k.tobytes() for k in c.keys], c.bidx, c.tokens,
+                            n_pages=c.src_pages, n_tokens=counts)
+    store = RecordStore(n, c.lay.record_bytes, DEV)
+    store.buf.fill_(0xA5)
+    ptrs = store.ptrs * torch.from_numpy(ptr_on.astype(np.int64)).to(DEV)
+    st = torch.zeros(n, dtype=torch.uint8, device=DEV)
+    blk = T.make_blocks(c.d_keys, c.d_bidx, c.d_tokens, i32(tables), i32(counts))
+    log("long digest tables", layers, "x", ppb, "pages,", n, "blocks")
+    for _ in range(2):  # the second save overwrites whole records
+        T.tl_save(c.ctx, torch.cuda.current_stream(), n, c.src.tl(), blk, ptrs, st)
+    torch.cuda.synchronize()
+    got, st = store.buf.cpu().numpy(), [int(x) for x in st.cpu()]
+    for b in range(n):
+        if ptr_on[b]:
+            assert st[b] == st_o[b] and got[b].tobytes() == recs_o[b], b
+        else:
+            assert st[b] == T.MISSING and (got[b] == 0xA5).all(), b
