@@ -125,3 +125,23 @@ def test_long_digest_tables(layers, ppb, n, odd):
             assert st[b] == st_o[b] and got[b].tobytes() == recs_o[b], b
         else:
             assert st[b] == T.MISSING and (got[b] == 0xA5).all(), b
+
+
+# The pass over verdicts takes 1,024 blocks at a time: counts around that, with
+# rejected blocks at its edges, and with every block rejected.
+@pytest.mark.parametrize("n,bad", [(1, [0]), (1023, [0, 1022]), (1024, [1023]), (1025, [1023, 1024]),
+                                   (2100, [0, 255, 256, 1024, 2047, 2048, 2099]), (1100, range(1100))])
+def test_rejected_blocks_at_tile_edges(n, bad):
+    geom = wl.Geometry(2, 1, 64, 8)
+    c = Case(geom, n, n, n + 3, seed=29)
+    c.make_src()
+    store, st = c.save()
+    assert (st == ref.ACCEPT).all()
+    recs = [bytearray(r.tobytes()) for r in store.buf.cpu().numpy()]
+    for i, b in enumerate(bad):
+        recs[b][(c.lay.payload_offset + 7) if i & 1 else 100] ^= 0x10
+    store2 = upload_records(recs, c.lay.record_bytes)
+    dst = random_fill(PagedCache(geom.n_layers, n + 3, c.stride, DEV), 3)
+    hk0, hv0 = host_layers(dst)
+    vo = check_restore(c, [bytes(r) for r in recs], store2.ptrs, store2.lens, c.t_dst, dst, hk0, hv0)
+    assert sorted(b for b in range(n) if vo[b] != ref.ACCEPT) == sorted(bad)
