@@ -700,8 +700,8 @@ __global__ __launch_bounds__(64 * kSegWaves) void k_save_slice(SliceArgs a) {
 }
 
 // ---- load ---------------------------------------------------------------------
-// A load is three launches. k_load_init clears the per-block status words.
-// k_load_main runs, in one grid, one metadata item per block (pointer, length,
+// A load is three launches (one for small blocks, see k_load_block).
+// k_load_init clears the per-block status words. k_load_main runs, in one grid, one metadata item per block (pointer, length,
 // root, header, position, key and token checks) and one chunk item per
 // (block, chunk) read (fused copy + digest + compare). Chunk items do not wait
 // for their block's metadata item: they copy whenever the record's pointer and
@@ -712,11 +712,18 @@ __global__ __launch_bounds__(256) void k_load_init(uint32_t* status, uint32_t n)
   for (uint32_t i = blockIdx.x * 256 + threadIdx.x; i < n; i += gridDim.x * 256) status[i] = 0;
 }
 
+// LDS written by a wavefront is seen by its own later reads.
+__device__ __forceinline__ void wave_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 // Metadata checks of block b by one wavefront, staging through `tile64`
-// (kMetaTile bytes of LDS). The workgroup must be this one wavefront: the
-// tile barriers are workgroup barriers.
-__device__ __forceinline__ void load_meta_item(const MetaArgs& a, uint32_t b, uint32_t lane,
-                                               uint64_t* tile64) {
+// (kMetaTile bytes of LDS, this wavefront's own). Returns the verdict code of
+// the first failing check, or 0.
+__device__ __forceinline__ uint32_t load_meta_item(const MetaArgs& a, uint32_t b, uint32_t lane,
+                                                   uint64_t* tile64) {
   const uint32_t* tile32 = (const uint32_t*)tile64;
   const uint64_t rec = a.rec[b];
   const uint64_t len = a.len[b];
@@ -733,10 +740,7 @@ __device__ __forceinline__ void load_meta_item(const MetaArgs& a, uint32_t b, ui
   } else if (len > a.g.record_bytes) {
     code = TL_OVERLONG;
   }
-  if (code) {
-    if (lane == 0) atomicOr(&a.status[b], code);
-    return;
-  }
+  if (code) return code;
   const uint32_t meta = (uint32_t)a.g.payload_offset;
   const uint32_t* key32 = (const uint32_t*)(a.keys + 32ull * b);
   const uint32_t* tok = a.tokens ? a.tokens + (uint64_t)a.g.block_tokens * b : nullptr;
@@ -749,7 +753,7 @@ __device__ __forceinline__ void load_meta_item(const MetaArgs& a, uint32_t b, ui
     const v4u* s = (const v4u*)(rec + off);
     v4u* t4 = (v4u*)tile64;
     for (uint32_t i = lane; i < nb / 16; i += 64) t4[i] = s[i];
-    __syncthreads();
+    wave_sync();
     if (off == 0) stored_root = tile64[tl::kRootOffset / 8];
     for (uint32_t wd = lane; wd < nb / 4; wd += 64) {
       const uint32_t o = off + 4 * wd;
@@ -772,7 +776,7 @@ __device__ __forceinline__ void load_meta_item(const MetaArgs& a, uint32_t b, ui
       }
     }
     hash_tile(tile64, nb, off, lane, acc);
-    __syncthreads();
+    wave_sync();
   }
   bool root_bad = finish_root(acc, meta) != stored_root;
   hdr_bad = __any(hdr_bad);
@@ -786,25 +790,22 @@ __device__ __forceinline__ void load_meta_item(const MetaArgs& a, uint32_t b, ui
     key_bad = key_bad && !(a.disabled & TL_CHECK_KEY);
     tok_bad = tok_bad && !(a.disabled & TL_CHECK_TOKENS);
   }
-  code = root_bad ? TL_ROOT : hdr_bad ? TL_HEADER : pos_bad ? TL_POSITION : key_bad ? TL_KEY
+  return root_bad ? TL_ROOT : hdr_bad ? TL_HEADER : pos_bad ? TL_POSITION : key_bad ? TL_KEY
                                                                           : tok_bad ? TL_TOKENS : 0;
-  if (lane == 0 && code) atomicOr(&a.status[b], code);
 }
 
-// Chunk item w: copy the chunk to its page, digest it on the way, compare
-// with the stored digest. Records with a bad pointer or length are never read.
-__device__ __forceinline__ void load_chunk_item(const SegArgs& a, uint32_t w, uint32_t lane) {
-  const Item it = decode(a, w);
-  if (!page_in_range(it.page, a.n_pages)) return;  // -1: not restored; else BADARG
+// Copies a chunk to its page, digests it on the way and compares with the
+// stored digest; false if it differs. Records with a bad pointer or length are
+// never read, and pages out of range (-1: not restored) never written.
+template <int B, int PF>
+__device__ __forceinline__ bool load_chunk(const SegArgs& a, const Item& it, uint32_t lane) {
+  if (!page_in_range(it.page, a.n_pages)) return true;
   const uint64_t rec = a.rec[it.b];
-  if (rec == 0 || (rec & 15) || a.len[it.b] != a.g.record_bytes) return;
-  const uint64_t leaf = copy_hash<TL_BATCH_ROWS, TL_PREFETCH>(record_chunk(a, rec, it), page_chunk(a, it),
-                                                              it.rows, lane);
+  if (rec == 0 || (rec & 15) || a.len[it.b] != a.g.record_bytes) return true;
+  const uint64_t leaf = copy_hash<B, PF>(record_chunk(a, rec, it), page_chunk(a, it), it.rows, lane);
   const uint64_t digest = wave_sum64(leaf);
-  if (lane == 0) {
-    const uint64_t want = *(const uint64_t*)(rec + tl::kHeaderBytes + 8ull * it.t);
-    if (want != digest && !(a.disabled & TL_CHECK_SEGMENT)) atomicOr(&a.status[it.b], kSegFailBit);
-  }
+  const uint64_t want = *(const uint64_t*)(rec + tl::kHeaderBytes + 8ull * it.t);
+  return want == digest || (a.disabled & TL_CHECK_SEGMENT);
 }
 
 struct LoadArgs {
@@ -813,16 +814,60 @@ struct LoadArgs {
 };
 
 // Items [0, n) are metadata items, [n, n + n * chunks) chunk items; one
-// wavefront per workgroup (see load_meta_item).
-__global__ __launch_bounds__(64) void k_load_main(LoadArgs a) {
-  __shared__ uint64_t tile64[kMetaTile / 8];
+// wavefront per workgroup.
+template <int B, int PF>
+__device__ __forceinline__ void load_items(const LoadArgs& a, uint64_t* tile64) {
   const uint32_t lane = threadIdx.x;
   const uint32_t n_meta = a.s.n;
   const uint32_t total = n_meta + a.s.total;
   for (uint32_t w = blockIdx.x; w < total; w += gridDim.x) {
-    if (w < n_meta) load_meta_item(a.m, w, lane, tile64);
-    else load_chunk_item(a.s, w - n_meta, lane);
+    if (w < n_meta) {
+      const uint32_t code = load_meta_item(a.m, w, lane, tile64);
+      if (code && lane == 0) atomicOr(&a.s.status[w], code);
+    } else {
+      const Item it = decode(a.s, w - n_meta);
+      if (!load_chunk<B, PF>(a.s, it, lane) && lane == 0) atomicOr(&a.s.status[it.b], kSegFailBit);
+    }
   }
+}
+
+__global__ __launch_bounds__(64) void k_load_main(LoadArgs a) {
+  __shared__ uint64_t tile64[kMetaTile / 8];
+  load_items<TL_BATCH_ROWS, TL_PREFETCH>(a, tile64);
+}
+
+// A load of small blocks in one launch: a workgroup per block, whose first
+// wavefront checks the metadata while the others copy a chunk each; the verdict
+// comes after a barrier, and a rejected block is zeroed by the wavefronts that
+// copied it. The status words are in LDS. What such a load costs is its
+// launches: 64 blocks of 8 chunks of 8 KiB 14.4 us against 19.2 with the three
+// kernels, 1,000 blocks 32.0 and 35.6, 4,096 blocks 111 and 118; 14 chunks of
+// 13 KiB, 40 blocks 14.2 and 18.8, 2,000 blocks 149 and 154. A wavefront copies
+// one chunk: with 32 of 8 KiB per block, two or three each, 77 blocks took 40.0
+// us and 37.0 with the three kernels, with 64 of 16 KiB 54.0 and 35.5.
+constexpr uint32_t kBlockChunks = 15;  // of 16 wavefronts, one checks the metadata
+
+__global__ __launch_bounds__(1024) void k_load_block(LoadArgs a, uint8_t* verdicts, uint32_t b0) {
+  __shared__ uint64_t tile64[kMetaTile / 8];
+  __shared__ uint32_t status[kBlockChunks + 1];
+  const uint32_t lane = threadIdx.x & 63, wave = uniform(threadIdx.x >> 6);
+  const uint32_t b = b0 + blockIdx.x;
+  const uint32_t item = b * a.s.g.n_seg + wave - 1;  // of wavefronts 1..n_seg
+  uint32_t st = 0;
+  if (wave == 0) {
+    st = load_meta_item(a.m, b, lane, tile64);
+  } else if (!load_chunk<16, 0>(a.s, decode(a.s, item), lane)) {
+    st = kSegFailBit;
+  }
+  if (lane == 0) status[wave] = st;
+  __syncthreads();
+  uint32_t all = 0;
+  for (uint32_t w = 0; w <= a.s.g.n_seg; ++w) all |= status[w];
+  const uint32_t code = (all & 0xff) ? (all & 0xff) : (all & kSegFailBit) ? TL_SEGMENT : TL_ACCEPT;
+  if (threadIdx.x == 0) verdicts[b] = (uint8_t)code;
+  if (code == TL_ACCEPT || wave == 0) return;
+  const Item it = decode(a.s, item);
+  if (page_in_range(it.page, a.s.n_pages)) zero_rows(page_chunk(a.s, it), it.rows, lane);
 }
 
 struct FinalArgs {
@@ -1130,12 +1175,24 @@ int launch_load(const tl_ctx* ctx, void* stream, size_t n, const uint64_t* d_rec
   f.parts = (uint32_t)std::min<uint64_t>(std::max(kFinalWgs / tiles, 1u), (tile_items + 3) / 4);
   const uint32_t n_items = (uint32_t)n + la.s.total;
   (void)hipGetLastError();
+  if (ctx->geo.n_seg <= kBlockChunks) {
+    la.s.order = 0;
+    constexpr size_t kGrid = 1u << 20;  // workgroups: a grid has fewer than 2^32 threads
+    for (size_t b0 = 0; b0 < n; b0 += kGrid) {
+      timed(TL_KERNEL_LOAD_MAIN, s, [&] {
+        hipLaunchKernelGGL(k_load_block, dim3((uint32_t)std::min(n - b0, kGrid)), dim3(64 * (1 + ctx->geo.n_seg)), 0, s, la,
+                           d_verdicts, (uint32_t)b0);
+      });
+    }
+    return launched();
+  }
   timed(TL_KERNEL_LOAD_INIT, s, [&] {
     const uint32_t g = (uint32_t)((n + 255) / 256);
     hipLaunchKernelGGL(k_load_init, dim3(g < 4096 ? g : 4096), dim3(256), 0, s, d_ws, (uint32_t)n);
   });
   timed(TL_KERNEL_LOAD_MAIN, s, [&] {
-    hipLaunchKernelGGL(k_load_main, dim3(n_items < (1u << 22) ? n_items : (1u << 22)), dim3(64), 0, s, la);
+    const dim3 grid(n_items < (1u << 22) ? n_items : (1u << 22));
+    hipLaunchKernelGGL(k_load_main, grid, dim3(64), 0, s, la);
   });
   timed(TL_KERNEL_LOAD_FINAL, s, [&] {
     hipLaunchKernelGGL(k_load_final, dim3(tiles * f.parts), dim3(256), 0, s, f);

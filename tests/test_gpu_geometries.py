@@ -127,12 +127,15 @@ def test_long_digest_tables(layers, ppb, n, odd):
             assert st[b] == T.MISSING and (got[b] == 0xA5).all(), b
 
 
-# The pass over verdicts takes 1,024 blocks at a time: counts around that, with
-# rejected blocks at its edges, and with every block rejected.
-@pytest.mark.parametrize("n,bad", [(1, [0]), (1023, [0, 1022]), (1024, [1023]), (1025, [1023, 1024]),
-                                   (2100, [0, 255, 256, 1024, 2047, 2048, 2099]), (1100, range(1100))])
-def test_rejected_blocks_at_tile_edges(n, bad):
-    geom = wl.Geometry(2, 1, 64, 8)
+# Blocks of at most 15 chunks are restored by one workgroup each (7 layers: 14
+# chunks), longer ones by the whole grid (8 layers: 16), whose pass over
+# verdicts takes 1,024 blocks at a time: counts around that, with rejected
+# blocks at its edges, and with every block rejected.
+@pytest.mark.parametrize("layers,n,bad", [(7, 3, [0]), (8, 1, [0]), (8, 1023, [0, 1022]), (8, 1024, [1023]),
+                                          (8, 1025, [1023, 1024]), (7, 1025, [0, 1024]),
+                                          (8, 2100, [0, 255, 256, 1024, 2047, 2048, 2099]), (8, 1100, range(1100))])
+def test_rejected_blocks_at_tile_edges(layers, n, bad):
+    geom = wl.Geometry(layers, 1, 64, 8)
     c = Case(geom, n, n, n + 3, seed=29)
     c.make_src()
     store, st = c.save()
@@ -145,3 +148,26 @@ def test_rejected_blocks_at_tile_edges(n, bad):
     hk0, hv0 = host_layers(dst)
     vo = check_restore(c, [bytes(r) for r in recs], store2.ptrs, store2.lens, c.t_dst, dst, hk0, hv0)
     assert sorted(b for b in range(n) if vo[b] != ref.ACCEPT) == sorted(bad)
+
+
+# Slabs of a 64-row chunk and a ragged one, in blocks of 12 chunks (a workgroup
+# per block) and of 20 (whole chunks in flight), with pages that are not
+# restored (nor read) and damage in a chunk of one that is.
+@pytest.mark.parametrize("layers", [3, 5])
+@pytest.mark.parametrize("rows", [65, 67, 96, 127])
+def test_ragged_chunks_of_small_and_large_blocks(layers, rows):
+    geom = wl.Geometry(layers, 2, 256, rows)
+    n = 5
+    c = Case(geom, n, n, n + 2, seed=31, stride_extra=48)
+    c.make_src()
+    store, _ = c.save()
+    recs = [bytearray(r.tobytes()) for r in store.buf.cpu().numpy()]
+    recs[1][c.lay.payload_offset + 70 * 1024 * layers] ^= 1
+    recs[3][-3] ^= 0x40
+    store2 = upload_records(recs, c.lay.record_bytes)
+    t_dst = c.t_dst.copy()
+    t_dst[:, [2, 3]] = -1
+    dst = random_fill(PagedCache(geom.n_layers, n + 2, c.stride, DEV), 3)
+    hk0, hv0 = host_layers(dst)
+    vo = check_restore(c, [bytes(r) for r in recs], store2.ptrs, store2.lens, t_dst, dst, hk0, hv0)
+    assert vo == [ref.ACCEPT, ref.SEGMENT, ref.ACCEPT, ref.ACCEPT, ref.ACCEPT]
