@@ -125,7 +125,10 @@ __device__ __forceinline__ void st16(gv4u* p, v4u v) {
 }
 
 // ---- XXH64 pieces --------------------------------------------------------
-__device__ __forceinline__ uint64_t rotl64(uint64_t x, int r) { return (x << r) | (x >> (64 - r)); }
+__device__ __forceinline__ uint64_t rotl64(uint64_t x, int r) {  // 0 < r < 32: one funnel shift per half
+  const uint32_t lo = (uint32_t)x, hi = (uint32_t)(x >> 32);
+  return (uint64_t)__builtin_amdgcn_alignbit(hi, lo, 32 - r) << 32 | __builtin_amdgcn_alignbit(lo, hi, 32 - r);
+}
 
 __device__ __forceinline__ uint64_t xx_round(uint64_t acc, uint64_t in) {
   acc += in * kP2;
@@ -493,28 +496,32 @@ k_save_seg_shared(SegArgs a) {
   save_chunks<TL_SHARED_SAVE_BATCH_ROWS, 0>(a, blockIdx.x, gridDim.x);
 }
 
-// Root checksum over one metadata tile already staged in LDS: lane k (k < 4)
-// runs XXH64 accumulator k over the k-th 8 bytes of every 32-byte stripe.
-__device__ __forceinline__ void hash_tile(const uint64_t* tile64, uint32_t n_bytes, uint32_t off,
-                                          uint32_t lane, uint64_t& acc) {
+// Root checksum over one metadata tile staged in LDS: lane k (k < 4) runs
+// XXH64 accumulator k over the k-th 8 bytes of every 32-byte stripe. The words
+// are already multiplied by P2 (the product does not depend on the
+// accumulator, so whoever stages the tile makes it); the root's word is zero,
+// and so is its product. The chain of rounds is all that counts here: eight
+// words are read ahead of it.
+__device__ __forceinline__ void hash_tile(const uint64_t* tile64, uint32_t n_bytes, uint32_t lane, uint64_t& acc) {
   if (lane < 4) {
-    const uint32_t stripes = n_bytes / 32;
-    for (uint32_t st = 0; st < stripes; ++st) {
-      uint64_t x = tile64[st * 4 + lane];
-      if (off + st * 32 + lane * 8 == tl::kRootOffset) x = 0;  // the root reads as zero
-      acc = xx_round(acc, x);
+    const uint32_t stripes = n_bytes / 32;  // a multiple of 8 but for the slices of a save
+    const uint64_t* p = tile64 + lane;
+    uint64_t x[8], y[8];
+    uint32_t st = 0;
+    if (stripes >= 8) {
+#pragma unroll
+      for (int i = 0; i < 8; ++i) x[i] = p[4 * i];
+      for (; st + 8 <= stripes; st += 8) {
+        const uint32_t next = st + 16 <= stripes ? st + 8 : st;
+#pragma unroll
+        for (int i = 0; i < 8; ++i) y[i] = p[4 * (next + i)];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) acc = rotl64(acc + x[i], 31) * kP1;
+#pragma unroll
+        for (int i = 0; i < 8; ++i) x[i] = y[i];
+      }
     }
-  }
-}
-
-// The same over a tile whose words were already multiplied by P2 (the
-// product does not depend on the accumulator, so the threads that stage the
-// tile compute it); the root's word is zero, and so is its product.
-__device__ __forceinline__ void hash_tile_premul(const uint64_t* tile64, uint32_t n_bytes, uint32_t lane,
-                                                 uint64_t& acc) {
-  if (lane < 4) {
-    const uint32_t stripes = n_bytes / 32;
-    for (uint32_t st = 0; st < stripes; ++st) acc = rotl64(acc + tile64[st * 4 + lane], 31) * kP1;
+    for (; st < stripes; ++st) acc = rotl64(acc + p[4 * st], 31) * kP1;
   }
 }
 
@@ -606,7 +613,7 @@ __device__ __forceinline__ void meta_hash(const MetaArgs& a, const MetaWords& m,
   __syncthreads();
   for (uint32_t off = from, t = 0; off < to; off += kMetaTile, ++t) {
     if (off + kMetaTile < to) stage(off + kMetaTile, tile[(t + 1) & 1]);
-    if (tid < 64) hash_tile_premul(tile[t & 1], min(to - off, kMetaTile), tid, acc);
+    if (tid < 64) hash_tile(tile[t & 1], min(to - off, kMetaTile), tid, acc);
     __syncthreads();
   }
 }
@@ -722,9 +729,15 @@ __device__ __forceinline__ void wave_sync() {
 // Metadata checks of block b by one wavefront, staging through `tile64`
 // (kMetaTile bytes of LDS, this wavefront's own). Returns the verdict code of
 // the first failing check, or 0.
+//
+// It is a chain of memory waits and of the root's rounds, 35 ns per 32 bytes,
+// and a small load or one of long digest tables waits for it. With the words
+// staged raw and each lane comparing one word at a time, the rounds took 100 ns
+// and every check its own wait: 8 blocks of 400 chunks (6.6 KB of metadata)
+// 34.8 us against 19.7 so, one block of 550 pages (563 KB) 2,175 against 1,671,
+// 1,000 blocks of 8 chunks (512 bytes) 31.0 against 28.2.
 __device__ __forceinline__ uint32_t load_meta_item(const MetaArgs& a, uint32_t b, uint32_t lane,
                                                    uint64_t* tile64) {
-  const uint32_t* tile32 = (const uint32_t*)tile64;
   const uint64_t rec = a.rec[b];
   const uint64_t len = a.len[b];
   // every lane takes part in the page-id check, so evaluate it up front
@@ -748,36 +761,81 @@ __device__ __forceinline__ uint32_t load_meta_item(const MetaArgs& a, uint32_t b
   bool hdr_bad = false, pos_bad = false, key_bad = false, tok_bad = false;
   uint64_t stored_root = 0;
   uint64_t acc = root_init(lane);
-  for (uint32_t off = 0; off < meta; off += kMetaTile) {
-    const uint32_t nb = meta - off < kMetaTile ? meta - off : kMetaTile;
-    const v4u* s = (const v4u*)(rec + off);
-    v4u* t4 = (v4u*)tile64;
-    for (uint32_t i = lane; i < nb / 16; i += 64) t4[i] = s[i];
-    wave_sync();
-    if (off == 0) stored_root = tile64[tl::kRootOffset / 8];
-    for (uint32_t wd = lane; wd < nb / 4; wd += 64) {
-      const uint32_t o = off + 4 * wd;
-      const uint32_t x = tile32[wd];
-      if (o < tl::kHeaderBytes) {
-        if (o == tl::kIndexOffset) pos_bad |= x != (uint32_t)bi;
-        else if (o == tl::kIndexOffset + 4) pos_bad |= x != (uint32_t)(bi >> 32);
-        else if (o >= tl::kKeyOffset && o < tl::kKeyOffset + 32) key_bad |= x != key32[(o - tl::kKeyOffset) / 4];
-        else if (o == tl::kRootOffset || o == tl::kRootOffset + 4) {}
-        else if (o == tl::kTailOffset) hdr_bad |= x != (tk < a.g.block_tokens ? tk : 0);
-        else hdr_bad |= x != a.tmpl[o / 4];
-      } else if (o < a.g.tok_off) {
-        // chunk digests: checked by the chunk items, covered by the root
-      } else if (o < a.g.tok_end) {
-        const uint32_t wi = (o - a.g.tok_off) / 4;
-        if (wi >= tk) hdr_bad |= x != 0;  // the padding after a partial block's tokens
-        else if (tok) tok_bad |= x != tok[wi];
-      } else {
-        hdr_bad |= x != 0;
+  // A granule and the words it has to hold are loaded together and without
+  // branches, so that a tile costs one wait for memory; the next tile's are on
+  // their way while this one is hashed.
+  constexpr uint32_t kPer = kMetaTile / (16 * 64);
+  v4u x[kPer], want[kPer];
+  auto fetch = [&](uint32_t off) {
+#pragma unroll
+    for (uint32_t i = 0; i < kPer; ++i) {
+      const uint32_t o = off + 16 * (lane + 64 * i);
+      if (o >= meta) continue;
+      x[i] = *(const v4u*)(rec + o);
+      if (tok && o + 16 > a.g.tok_off) {
+#pragma unroll
+        for (uint32_t j = 0; j < 4; ++j) {
+          const uint32_t q = max(o + 4 * j, a.g.tok_off);
+          want[i][j] = tok[min((q - a.g.tok_off) / 4, a.g.block_tokens - 1)];
+        }
       }
     }
-    hash_tile(tile64, nb, off, lane, acc);
+  };
+  fetch(0);
+  v4u head;  // lanes 0-15: the header granule that the record has to hold
+  {
+    const uint32_t w0 = 4 * (lane & 15), key0 = tl::kKeyOffset / 4;
+#pragma unroll
+    for (uint32_t j = 0; j < 4; ++j) {
+      const uint32_t t = a.tmpl[w0 + j], k = key32[(w0 + j - key0) & 7];
+      head[j] = w0 + j - key0 < 8 ? k : t;
+    }
+    if (w0 == tl::kIndexOffset / 4) {  // (the granule's other half is the key's)
+      head.x = (uint32_t)bi;
+      head.y = (uint32_t)(bi >> 32);
+    }
+    if (w0 == tl::kRootOffset / 4) head.w = tk < a.g.block_tokens ? tk : 0;  // the root is zero in the template
+  }
+  for (uint32_t off = 0; off < meta; off += kMetaTile) {
+#pragma unroll
+    for (uint32_t i = 0; i < kPer; ++i) {
+      const uint32_t at = lane + 64 * i, o = off + 16 * at;
+      if (o >= meta) continue;
+      if (o == tl::kRootOffset) {  // reads as zero
+        stored_root = lo64(x[i]);
+        x[i].x = x[i].y = 0;
+      }
+      if (o < tl::kHeaderBytes) {
+#pragma unroll
+        for (uint32_t j = 0; j < 4; ++j) {
+          const uint32_t q = o + 4 * j;
+          const bool bad = x[i][j] != head[j], pos = q - tl::kIndexOffset < 8, key = q - tl::kKeyOffset < 32;
+          pos_bad |= bad & pos;
+          key_bad |= bad & key;
+          hdr_bad |= bad & !pos & !key;
+        }
+      } else if (o + 16 > a.g.tok_off) {
+        // (chunk digests before the token ids: checked by the chunk items,
+        // covered by the root)
+#pragma unroll
+        for (uint32_t j = 0; j < 4; ++j) {
+          const uint32_t q = o + 4 * j, v = x[i][j];
+          const bool ids = q < a.g.tok_end && (q - a.g.tok_off) / 4 < tk;
+          hdr_bad |= q >= a.g.tok_off & !ids & v != 0;  // padding, also after a partial block's tokens
+          tok_bad |= q >= a.g.tok_off & ids & tok != nullptr & v != want[i][j];
+        }
+      }
+      tile64[2 * at] = lo64(x[i]) * kP2;
+      tile64[2 * at + 1] = hi64(x[i]) * kP2;
+    }
+    wave_sync();
+    if (off + kMetaTile < meta) fetch(off + kMetaTile);
+    hash_tile(tile64, min(meta - off, kMetaTile), lane, acc);
     wave_sync();
   }
+  static_assert(tl::kIndexOffset % 16 == 0 && tl::kKeyOffset == tl::kIndexOffset + 8 && tl::kRootOffset % 16 == 0 &&
+                    tl::kTailOffset == tl::kRootOffset + 12, "the header's granules are as the checks take them");
+  stored_root = readlane64(stored_root, tl::kRootOffset / 16);
   bool root_bad = finish_root(acc, meta) != stored_root;
   hdr_bad = __any(hdr_bad);
   pos_bad = __any(pos_bad);
@@ -851,8 +909,8 @@ __global__ __launch_bounds__(64) void k_load_main_deep(LoadArgs a) {
 // wavefront checks the metadata while the others copy a chunk each; the verdict
 // comes after a barrier, and a rejected block is zeroed by the wavefronts that
 // copied it. The status words are in LDS. What such a load costs is its
-// launches: 64 blocks of 8 chunks of 8 KiB 14.4 us against 19.2 with the three
-// kernels, 1,000 blocks 32.0 and 35.6, 4,096 blocks 111 and 118; 14 chunks of
+// launches: 64 blocks of 8 chunks of 8 KiB 13.5 us against 19.2 with the three
+// kernels, 1,000 blocks 28.2 and 35.5, 4,096 blocks 104 and 118; 14 chunks of
 // 13 KiB, 40 blocks 14.2 and 18.8, 2,000 blocks 149 and 154. A wavefront copies
 // one chunk: with 32 of 8 KiB per block, two or three each, 77 blocks took 40.0
 // us and 37.0 with the three kernels, with 64 of 16 KiB 54.0 and 35.5.
