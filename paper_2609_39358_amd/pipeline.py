@@ -211,11 +211,31 @@ class DeviceStore:
             ptrs = self.records.ptrs.index_select(0, d_slots)
             T.tl_save(self.ctx, stream, n, src.tl(),
                       T.make_blocks(d_keys, d_positions, d_tokens, d_tables, d_n_tokens), ptrs, status)
-            if not bool((status[:n] == T.ACCEPT).all()):
+            # the smallest status is the good one, so the sum tells whether there is another
+            total = status[:n].sum()
+            # the fingerprints change nothing of the store: enqueued while the save runs
+            fps = self._fingerprints(d_tokens, d_positions, n, stream, d_n_tokens)
+            if int(total) != n * T.ACCEPT:
                 raise RuntimeError("save refused some blocks (bad page ids)")
             self.records.lens.index_fill_(0, d_slots, self.ctx.record_bytes)
-            self.add(d_keys, d_tokens, d_positions, d_slots, stream, d_n_tokens)
+            self._index(d_keys, fps, d_slots, stream)
         return status[:n]
+
+    def _fingerprints(self, d_tokens, d_positions, n: int, stream, d_n_tokens) -> torch.Tensor:
+        fps = torch.empty((n, 32), dtype=torch.uint8, device=self.device)
+        T.tl_block_fingerprints(self.ctx, stream, n, d_tokens, d_positions, fps, d_n_tokens)
+        return fps
+
+    def _index(self, d_keys, fps, d_slots, stream):
+        n = d_keys.shape[0]
+        self.slot_keys.index_copy_(0, d_slots, d_keys)
+        wsb = T.tl_dindex_workspace_bytes(n)
+        ws = torch.empty(wsb, dtype=torch.uint8, device=self.device)
+        st = torch.empty(n, dtype=torch.uint8, device=self.device)
+        for idx, k in ((self.key_index, d_keys), (self.token_index, fps)):
+            idx.put(stream, n, k, d_slots, st, ws, wsb)
+            if int(st.sum()) != n * T.TL_INDEX_STORED:  # the smallest status, as in save_blocks
+                raise RuntimeError("device index refused keys (full or tag clash)")
 
     def add(self, d_keys: torch.Tensor, d_tokens: torch.Tensor, d_positions: torch.Tensor,
             d_slots: torch.Tensor, stream=None, d_n_tokens: torch.Tensor = None):
@@ -227,16 +247,7 @@ class DeviceStore:
         if n == 0:
             return
         with _on(stream):
-            self.slot_keys.index_copy_(0, d_slots, d_keys)
-            fps = torch.empty((n, 32), dtype=torch.uint8, device=self.device)
-            T.tl_block_fingerprints(self.ctx, stream, n, d_tokens, d_positions, fps, d_n_tokens)
-            wsb = T.tl_dindex_workspace_bytes(n)
-            ws = torch.empty(wsb, dtype=torch.uint8, device=self.device)
-            st = torch.empty(n, dtype=torch.uint8, device=self.device)
-            for idx, k in ((self.key_index, d_keys), (self.token_index, fps)):
-                idx.put(stream, n, k, d_slots, st, ws, wsb)
-                if not bool((st == T.TL_INDEX_STORED).all()):
-                    raise RuntimeError("device index refused keys (full or tag clash)")
+            self._index(d_keys, self._fingerprints(d_tokens, d_positions, n, stream, d_n_tokens), d_slots, stream)
 
 
 @dataclass

@@ -308,6 +308,8 @@ def _fits(x, nbytes: int, what: str):
     caller's responsibility, as in the C ABI."""
     if x is None or isinstance(x, int) or not hasattr(x, "data_ptr"):
         return
+    if getattr(x, "is_cuda", False) and x.is_contiguous() and x.nbytes >= nbytes:
+        return
     if x.device.type != "cuda":
         raise ValueError("%s must be device memory, got a %s tensor" % (what, x.device.type))
     if not x.is_contiguous():
