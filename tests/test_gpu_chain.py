@@ -230,6 +230,22 @@ def test_device_index_random_batches(seed):
         assert n_used == len(model) <= cap and 0 <= maxp < 1024
 
 
+@pytest.mark.parametrize("n", [1, 63, 64, 511, 512, 513])
+def test_device_index_put_sizes(n):
+    """Puts around the size up to which one workgroup does all three phases:
+    every key twice in the call, then half of them overwritten."""
+    idx = new_index(1024)
+    keys = rand_keys((n + 1) // 2, 900 + n)
+    batch = (keys + keys)[:n]
+    assert (dput(idx, batch, range(n)) == T.TL_INDEX_STORED).all()
+    want = ref.index_put({}, batch, range(n))
+    assert dget(idx, keys) == [want[k] for k in keys] and dstats(idx)[0] == len(keys)
+    some = keys[::2]
+    assert (dput(idx, some, range(5000, 5000 + len(some))) == T.TL_INDEX_STORED).all()
+    ref.index_put(want, some, range(5000, 5000 + len(some)))
+    assert dget(idx, keys) == [want[k] for k in keys] and dstats(idx)[0] == len(keys)
+
+
 def stored_docs(ns, bt, n_docs, blocks_per_doc, seed):
     docs = [wl.tokens(blocks_per_doc * bt, seed + d) for d in range(n_docs)]
     keys = [ref.block_keys(ns, d.tobytes(), 4 * bt) for d in docs]
