@@ -98,7 +98,8 @@ constexpr uint64_t kP5 = 0x27D4EB2F165667C5ull;
 #endif
 
 constexpr uint32_t kSegWaves = TL_SEG_WAVES;
-constexpr uint32_t kMetaTile = 4096;    // metadata bytes staged in LDS at a time
+constexpr uint32_t kMetaTile = 4096;    // metadata bytes staged in LDS at a time (save)
+constexpr uint32_t kLoadTile = 1024;    // by one wavefront of a load (4096: 0.1 to 0.4 us slower for 8 to 64 blocks)
 constexpr uint32_t kSegFailBit = 0x100; // status bit: some chunk digest mismatched
 
 // 16 bytes per lane: a native vector so that the compiler emits dwordx4
@@ -727,7 +728,7 @@ __device__ __forceinline__ void wave_sync() {
 }
 
 // Metadata checks of block b by one wavefront, staging through `tile64`
-// (kMetaTile bytes of LDS, this wavefront's own). Returns the verdict code of
+// (kLoadTile bytes of LDS, this wavefront's own). Returns the verdict code of
 // the first failing check, or 0.
 //
 // It is a chain of memory waits and of the root's rounds, 35 ns per 32 bytes,
@@ -764,7 +765,7 @@ __device__ __forceinline__ uint32_t load_meta_item(const MetaArgs& a, uint32_t b
   // A granule and the words it has to hold are loaded together and without
   // branches, so that a tile costs one wait for memory; the next tile's are on
   // their way while this one is hashed.
-  constexpr uint32_t kPer = kMetaTile / (16 * 64);
+  constexpr uint32_t kPer = kLoadTile / (16 * 64);
   v4u x[kPer], want[kPer];
   auto fetch = [&](uint32_t off) {
 #pragma unroll
@@ -796,7 +797,7 @@ __device__ __forceinline__ uint32_t load_meta_item(const MetaArgs& a, uint32_t b
     }
     if (w0 == tl::kRootOffset / 4) head.w = tk < a.g.block_tokens ? tk : 0;  // the root is zero in the template
   }
-  for (uint32_t off = 0; off < meta; off += kMetaTile) {
+  for (uint32_t off = 0; off < meta; off += kLoadTile) {
 #pragma unroll
     for (uint32_t i = 0; i < kPer; ++i) {
       const uint32_t at = lane + 64 * i, o = off + 16 * at;
@@ -829,8 +830,8 @@ __device__ __forceinline__ uint32_t load_meta_item(const MetaArgs& a, uint32_t b
       tile64[2 * at + 1] = hi64(x[i]) * kP2;
     }
     wave_sync();
-    if (off + kMetaTile < meta) fetch(off + kMetaTile);
-    hash_tile(tile64, min(meta - off, kMetaTile), lane, acc);
+    if (off + kLoadTile < meta) fetch(off + kLoadTile);
+    hash_tile(tile64, min(meta - off, kLoadTile), lane, acc);
     wave_sync();
   }
   static_assert(tl::kIndexOffset % 16 == 0 && tl::kKeyOffset == tl::kIndexOffset + 8 && tl::kRootOffset % 16 == 0 &&
@@ -890,7 +891,7 @@ __device__ __forceinline__ void load_items(const LoadArgs& a, uint64_t* tile64) 
 }
 
 __global__ __launch_bounds__(64) void k_load_main(LoadArgs a) {
-  __shared__ uint64_t tile64[kMetaTile / 8];
+  __shared__ uint64_t tile64[kLoadTile / 8];
   load_items<TL_BATCH_ROWS, TL_PREFETCH>(a, tile64);
 }
 
@@ -901,7 +902,7 @@ __global__ __launch_bounds__(64) void k_load_main(LoadArgs a) {
 // 96 KiB slabs, 1,500 blocks 1,414 -> 1,391. Slabs of one chunk gain nothing
 // (500 blocks of 120 64 KiB slabs 1,539 and 1,546 us, 32 KiB slabs 417 and 417).
 __global__ __launch_bounds__(64) void k_load_main_deep(LoadArgs a) {
-  __shared__ uint64_t tile64[kMetaTile / 8];
+  __shared__ uint64_t tile64[kLoadTile / 8];
   load_items<64, 0>(a, tile64);
 }
 
@@ -917,7 +918,7 @@ __global__ __launch_bounds__(64) void k_load_main_deep(LoadArgs a) {
 constexpr uint32_t kBlockChunks = 15;  // of 16 wavefronts, one checks the metadata
 
 __global__ __launch_bounds__(1024) void k_load_block(LoadArgs a, uint8_t* verdicts, uint32_t b0) {
-  __shared__ uint64_t tile64[kMetaTile / 8];
+  __shared__ uint64_t tile64[kLoadTile / 8];
   __shared__ uint32_t status[kBlockChunks + 1];
   const uint32_t lane = threadIdx.x & 63, wave = uniform(threadIdx.x >> 6);
   const uint32_t b = b0 + blockIdx.x;
