@@ -98,8 +98,8 @@ constexpr uint64_t kP5 = 0x27D4EB2F165667C5ull;
 #endif
 
 constexpr uint32_t kSegWaves = TL_SEG_WAVES;
-constexpr uint32_t kMetaTile = 4096;    // metadata bytes staged in LDS at a time (save)
-constexpr uint32_t kLoadTile = 1024;    // by one wavefront of a load (4096: 0.1 to 0.4 us slower for 8 to 64 blocks)
+constexpr uint32_t kMetaTile = 4096;    // metadata bytes staged in LDS at a time
+constexpr uint32_t kLoadTile = 1024;    // by a wavefront that is waited for (4096: 0.1 to 0.4 us slower for 8 to 64 blocks)
 constexpr uint32_t kSegFailBit = 0x100; // status bit: some chunk digest mismatched
 
 // 16 bytes per lane: a native vector so that the compiler emits dwordx4
@@ -126,19 +126,28 @@ __device__ __forceinline__ void st16(gv4u* p, v4u v) {
 }
 
 // ---- XXH64 pieces --------------------------------------------------------
-__device__ __forceinline__ uint64_t rotl64(uint64_t x, int r) {  // 0 < r < 32: one funnel shift per half
+// Rotation by 0 < r < 32. kFunnel: one funnel shift per half, the shorter chain,
+// which the root and the digests of a save take (four blocks of 8,192 chunks of
+// 1 KiB saved in 230 us, 244 with 64-bit shifts). The copy loops of a load are
+// faster with 64-bit shifts and the schedule that they give (300 blocks of 64
+// chunks of 16 KiB 121.9 us with funnel shifts, 120.8 so).
+template <bool kFunnel = true>
+__device__ __forceinline__ uint64_t rotl64(uint64_t x, int r) {
+  if constexpr (!kFunnel) return (x << r) | (x >> (64 - r));
   const uint32_t lo = (uint32_t)x, hi = (uint32_t)(x >> 32);
   return (uint64_t)__builtin_amdgcn_alignbit(hi, lo, 32 - r) << 32 | __builtin_amdgcn_alignbit(lo, hi, 32 - r);
 }
 
+template <bool kFunnel = true>
 __device__ __forceinline__ uint64_t xx_round(uint64_t acc, uint64_t in) {
   acc += in * kP2;
-  acc = rotl64(acc, 31);
+  acc = rotl64<kFunnel>(acc, 31);
   return acc * kP1;
 }
 
+template <bool kFunnel = true>
 __device__ __forceinline__ uint64_t xx_merge(uint64_t acc, uint64_t v) {
-  acc ^= xx_round(0, v);
+  acc ^= xx_round<kFunnel>(0, v);
   return acc * kP1 + kP4;
 }
 
@@ -155,6 +164,7 @@ __device__ __forceinline__ uint64_t lo64(v4u v) { return (uint64_t)v.y << 32 | v
 __device__ __forceinline__ uint64_t hi64(v4u v) { return (uint64_t)v.w << 32 | v.z; }
 
 // XXH64 state of one lane's column.
+template <bool kFunnel>
 struct Column {
   uint64_t v1, v2, v3, v4;
   __device__ __forceinline__ void init(uint64_t seed) {
@@ -165,29 +175,29 @@ struct Column {
   }
   // one 32-byte stripe = two consecutive granules of the column
   __device__ __forceinline__ void stripe(v4u a, v4u b) {
-    v1 = xx_round(v1, lo64(a));
-    v2 = xx_round(v2, hi64(a));
-    v3 = xx_round(v3, lo64(b));
-    v4 = xx_round(v4, hi64(b));
+    v1 = xx_round<kFunnel>(v1, lo64(a));
+    v2 = xx_round<kFunnel>(v2, hi64(a));
+    v3 = xx_round<kFunnel>(v3, lo64(b));
+    v4 = xx_round<kFunnel>(v4, hi64(b));
   }
   // digest of a column of `rows` granules; `last` is the odd final granule
   __device__ __forceinline__ uint64_t finish(uint64_t seed, uint32_t rows, v4u last) const {
     uint64_t h;
     if (rows >= 2) {
-      h = rotl64(v1, 1) + rotl64(v2, 7) + rotl64(v3, 12) + rotl64(v4, 18);
-      h = xx_merge(h, v1);
-      h = xx_merge(h, v2);
-      h = xx_merge(h, v3);
-      h = xx_merge(h, v4);
+      h = rotl64<kFunnel>(v1, 1) + rotl64<kFunnel>(v2, 7) + rotl64<kFunnel>(v3, 12) + rotl64<kFunnel>(v4, 18);
+      h = xx_merge<kFunnel>(h, v1);
+      h = xx_merge<kFunnel>(h, v2);
+      h = xx_merge<kFunnel>(h, v3);
+      h = xx_merge<kFunnel>(h, v4);
     } else {
       h = seed + kP5;
     }
     h += (uint64_t)rows * 16;
     if (rows & 1) {
-      h ^= xx_round(0, lo64(last));
-      h = rotl64(h, 27) * kP1 + kP4;
-      h ^= xx_round(0, hi64(last));
-      h = rotl64(h, 27) * kP1 + kP4;
+      h ^= xx_round<kFunnel>(0, lo64(last));
+      h = rotl64<kFunnel>(h, 27) * kP1 + kP4;
+      h ^= xx_round<kFunnel>(0, hi64(last));
+      h = rotl64<kFunnel>(h, 27) * kP1 + kP4;
     }
     return xx_avalanche(h);
   }
@@ -323,8 +333,8 @@ __device__ __forceinline__ void load_batch(v4u (&x)[B], const gv4u* s, uint32_t 
 
 // Stores a batch of rows and feeds it, two rows (one 32-byte stripe) at a
 // time, to the lane's column state.
-template <int B>
-__device__ __forceinline__ void store_hash_batch(const v4u (&x)[B], gv4u* d, uint32_t r, Column& c) {
+template <int B, bool kFunnel>
+__device__ __forceinline__ void store_hash_batch(const v4u (&x)[B], gv4u* d, uint32_t r, Column<kFunnel>& c) {
 #pragma unroll
   for (int i = 0; i < B; ++i) st16(d + (uint64_t)(r + i) * 64, x[i]);
 #pragma unroll
@@ -333,9 +343,9 @@ __device__ __forceinline__ void store_hash_batch(const v4u (&x)[B], gv4u* d, uin
 
 // Rows left after the main batches: one batch of each halved size that fits
 // (a chunk has at most 64 rows, so each size runs at most once).
-template <int B>
+template <int B, bool kFunnel>
 __device__ __forceinline__ void tail_batches(const gv4u* s, gv4u* d, uint32_t rows, uint32_t& r,
-                                             Column& c) {
+                                             Column<kFunnel>& c) {
   if constexpr (B >= 2) {
     if (rows - r >= B) {
       v4u x[B];
@@ -351,13 +361,13 @@ __device__ __forceinline__ void tail_batches(const gv4u* s, gv4u* d, uint32_t ro
 // digest (seed = lane). Lane j moves granule j of every row. Rows go in
 // batches of B; with prefetching (PF), the next batch's loads are in flight
 // while the current batch is stored and hashed.
-template <int B, int PF>
+template <int B, int PF, bool kFunnel>
 __device__ __forceinline__ uint64_t copy_hash(const char* src, char* dst, uint32_t rows,
                                               uint32_t lane) {
   static_assert(B % 2 == 0, "batches hold whole stripes");
   const gv4u* s = (const gv4u*)src + lane;
   gv4u* d = (gv4u*)dst + lane;
-  Column c;
+  Column<kFunnel> c;
   c.init(lane);
   const uint32_t full = rows / B * B;
   uint32_t r = 0;
@@ -441,7 +451,7 @@ __device__ __forceinline__ bool block_pages_ok(const tl::Geo& g, const int32_t* 
 // them: the chunk stored for a page that a partial block leaves out.
 __device__ uint64_t zero_hash(char* dst, uint32_t rows, uint32_t lane) {
   gv4u* d = (gv4u*)dst + lane;
-  Column c;
+  Column<true> c;
   c.init(lane);
   const v4u z = zero4();
   uint32_t r = 0;
@@ -473,7 +483,7 @@ __device__ __forceinline__ void save_chunks(const SegArgs& a, uint32_t wg, uint3
     }
     const uint64_t leaf =
         it.page < 0 ? zero_hash(out, it.rows, lane)  // a page the partial block leaves out
-                    : copy_hash<B, PF>(page_chunk(a, it), out, it.rows, lane);
+                    : copy_hash<B, PF, true>(page_chunk(a, it), out, it.rows, lane);
     const uint64_t digest = wave_sum64(leaf);
     if (lane == 0) *(uint64_t*)(rec + tl::kHeaderBytes + 8ull * it.t) = digest;
   }
@@ -709,9 +719,11 @@ __global__ __launch_bounds__(64 * kSegWaves) void k_save_slice(SliceArgs a) {
 
 // ---- load ---------------------------------------------------------------------
 // A load is three launches (one for small blocks, see k_load_block).
-// k_load_init clears the per-block status words. k_load_main runs, in one grid, one metadata item per block (pointer, length,
-// root, header, position, key and token checks) and one chunk item per
-// (block, chunk) read (fused copy + digest + compare). Chunk items do not wait
+// k_load_init clears the per-block status words. k_load_main (or
+// k_load_main_meta, k_load_main_deep) runs, in one grid, one metadata item per
+// block (pointer, length, root, header, position, key and token checks) and one
+// chunk item per (block, chunk) read (fused copy + digest + compare). Chunk
+// items do not wait
 // for their block's metadata item: they copy whenever the record's pointer and
 // length allow reading it, and k_load_final, which turns the status words into
 // verdicts, zero-fills every page of a rejected block.
@@ -727,27 +739,27 @@ __device__ __forceinline__ void wave_sync() {
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-// Metadata checks of block b by one wavefront, staging through `tile64`
-// (kLoadTile bytes of LDS, this wavefront's own). Returns the verdict code of
-// the first failing check, or 0.
-//
-// It is a chain of memory waits and of the root's rounds, 35 ns per 32 bytes,
-// and a small load or one of long digest tables waits for it. With the words
-// staged raw and each lane comparing one word at a time, the rounds took 100 ns
-// and every check its own wait: 8 blocks of 400 chunks (6.6 KB of metadata)
-// 34.8 us against 19.7 so, one block of 550 pages (563 KB) 2,175 against 1,671,
-// 1,000 blocks of 8 chunks (512 bytes) 31.0 against 28.2.
-__device__ __forceinline__ uint32_t load_meta_item(const MetaArgs& a, uint32_t b, uint32_t lane,
-                                                   uint64_t* tile64) {
-  const uint64_t rec = a.rec[b];
+// Metadata checks of one block by one wavefront: what the checks compare with,
+// and what they found.
+struct MetaCheck {
+  uint64_t rec, bi;
+  uint32_t tk, meta;
+  const uint32_t* key32;
+  const uint32_t* tok;
+  bool hdr_bad = false, pos_bad = false, key_bad = false, tok_bad = false;
+};
+
+// The checks that read no metadata: the verdict code of the first failing one, or 0.
+__device__ __forceinline__ uint32_t meta_begin(const MetaArgs& a, uint32_t b, uint32_t lane, MetaCheck& c) {
+  c.rec = a.rec[b];
   const uint64_t len = a.len[b];
   // every lane takes part in the page-id check, so evaluate it up front
   const bool pages_ok = block_pages_ok(a.g, a.tables, a.n, b, a.n_pages, -1, lane, a.g.ppb);
-  const uint32_t tk = block_tok(a.g, a.n_tokens, b);
+  c.tk = block_tok(a.g, a.n_tokens, b);
   uint32_t code = 0;
-  if (rec == 0) {
+  if (c.rec == 0) {
     code = TL_MISSING;
-  } else if ((rec & 15) || !pages_ok || tk == 0) {
+  } else if ((c.rec & 15) || !pages_ok || c.tk == 0) {
     code = TL_BADARG;
   } else if (len < a.g.record_bytes) {
     code = TL_TRUNCATED;
@@ -755,93 +767,20 @@ __device__ __forceinline__ uint32_t load_meta_item(const MetaArgs& a, uint32_t b
     code = TL_OVERLONG;
   }
   if (code) return code;
-  const uint32_t meta = (uint32_t)a.g.payload_offset;
-  const uint32_t* key32 = (const uint32_t*)(a.keys + 32ull * b);
-  const uint32_t* tok = a.tokens ? a.tokens + (uint64_t)a.g.block_tokens * b : nullptr;
-  const uint64_t bi = a.bidx[b];
-  bool hdr_bad = false, pos_bad = false, key_bad = false, tok_bad = false;
-  uint64_t stored_root = 0;
-  uint64_t acc = root_init(lane);
-  // A granule and the words it has to hold are loaded together and without
-  // branches, so that a tile costs one wait for memory; the next tile's are on
-  // their way while this one is hashed.
-  constexpr uint32_t kPer = kLoadTile / (16 * 64);
-  v4u x[kPer], want[kPer];
-  auto fetch = [&](uint32_t off) {
-#pragma unroll
-    for (uint32_t i = 0; i < kPer; ++i) {
-      const uint32_t o = off + 16 * (lane + 64 * i);
-      if (o >= meta) continue;
-      x[i] = *(const v4u*)(rec + o);
-      if (tok && o + 16 > a.g.tok_off) {
-#pragma unroll
-        for (uint32_t j = 0; j < 4; ++j) {
-          const uint32_t q = max(o + 4 * j, a.g.tok_off);
-          want[i][j] = tok[min((q - a.g.tok_off) / 4, a.g.block_tokens - 1)];
-        }
-      }
-    }
-  };
-  fetch(0);
-  v4u head;  // lanes 0-15: the header granule that the record has to hold
-  {
-    const uint32_t w0 = 4 * (lane & 15), key0 = tl::kKeyOffset / 4;
-#pragma unroll
-    for (uint32_t j = 0; j < 4; ++j) {
-      const uint32_t t = a.tmpl[w0 + j], k = key32[(w0 + j - key0) & 7];
-      head[j] = w0 + j - key0 < 8 ? k : t;
-    }
-    if (w0 == tl::kIndexOffset / 4) {  // (the granule's other half is the key's)
-      head.x = (uint32_t)bi;
-      head.y = (uint32_t)(bi >> 32);
-    }
-    if (w0 == tl::kRootOffset / 4) head.w = tk < a.g.block_tokens ? tk : 0;  // the root is zero in the template
-  }
-  for (uint32_t off = 0; off < meta; off += kLoadTile) {
-#pragma unroll
-    for (uint32_t i = 0; i < kPer; ++i) {
-      const uint32_t at = lane + 64 * i, o = off + 16 * at;
-      if (o >= meta) continue;
-      if (o == tl::kRootOffset) {  // reads as zero
-        stored_root = lo64(x[i]);
-        x[i].x = x[i].y = 0;
-      }
-      if (o < tl::kHeaderBytes) {
-#pragma unroll
-        for (uint32_t j = 0; j < 4; ++j) {
-          const uint32_t q = o + 4 * j;
-          const bool bad = x[i][j] != head[j], pos = q - tl::kIndexOffset < 8, key = q - tl::kKeyOffset < 32;
-          pos_bad |= bad & pos;
-          key_bad |= bad & key;
-          hdr_bad |= bad & !pos & !key;
-        }
-      } else if (o + 16 > a.g.tok_off) {
-        // (chunk digests before the token ids: checked by the chunk items,
-        // covered by the root)
-#pragma unroll
-        for (uint32_t j = 0; j < 4; ++j) {
-          const uint32_t q = o + 4 * j, v = x[i][j];
-          const bool ids = q < a.g.tok_end && (q - a.g.tok_off) / 4 < tk;
-          hdr_bad |= q >= a.g.tok_off & !ids & v != 0;  // padding, also after a partial block's tokens
-          tok_bad |= q >= a.g.tok_off & ids & tok != nullptr & v != want[i][j];
-        }
-      }
-      tile64[2 * at] = lo64(x[i]) * kP2;
-      tile64[2 * at + 1] = hi64(x[i]) * kP2;
-    }
-    wave_sync();
-    if (off + kLoadTile < meta) fetch(off + kLoadTile);
-    hash_tile(tile64, min(meta - off, kLoadTile), lane, acc);
-    wave_sync();
-  }
-  static_assert(tl::kIndexOffset % 16 == 0 && tl::kKeyOffset == tl::kIndexOffset + 8 && tl::kRootOffset % 16 == 0 &&
-                    tl::kTailOffset == tl::kRootOffset + 12, "the header's granules are as the checks take them");
-  stored_root = readlane64(stored_root, tl::kRootOffset / 16);
-  bool root_bad = finish_root(acc, meta) != stored_root;
-  hdr_bad = __any(hdr_bad);
-  pos_bad = __any(pos_bad);
-  key_bad = __any(key_bad);
-  tok_bad = __any(tok_bad);
+  c.meta = (uint32_t)a.g.payload_offset;
+  c.key32 = (const uint32_t*)(a.keys + 32ull * b);
+  c.tok = a.tokens ? a.tokens + (uint64_t)a.g.block_tokens * b : nullptr;
+  c.bi = a.bidx[b];
+  return 0;
+}
+
+// The verdict code of the first failing check of the others, or 0.
+__device__ __forceinline__ uint32_t meta_end(const MetaArgs& a, const MetaCheck& c, uint64_t acc, uint64_t stored_root) {
+  bool root_bad = finish_root(acc, c.meta) != stored_root;
+  bool hdr_bad = __any(c.hdr_bad);
+  bool pos_bad = __any(c.pos_bad);
+  bool key_bad = __any(c.key_bad);
+  bool tok_bad = __any(c.tok_bad);
   if (a.disabled) {  // sabotage build: a switched-off check never fails
     root_bad = root_bad && !(a.disabled & TL_CHECK_ROOT);
     hdr_bad = hdr_bad && !(a.disabled & TL_CHECK_HEADER);
@@ -853,18 +792,170 @@ __device__ __forceinline__ uint32_t load_meta_item(const MetaArgs& a, uint32_t b
                                                                           : tok_bad ? TL_TOKENS : 0;
 }
 
-// Copies a chunk to its page, digests it on the way and compares with the
-// stored digest; false if it differs. Records with a bad pointer or length are
-// never read, and pages out of range (-1: not restored) never written.
-template <int B, int PF>
-__device__ __forceinline__ bool load_chunk(const SegArgs& a, const Item& it, uint32_t lane) {
-  if (!page_in_range(it.page, a.n_pages)) return true;
+// The simple form of the checks, staging through `tile64` (kMetaTile bytes of
+// LDS): words are staged raw and compared one at a time, 100 ns per 32 bytes of
+// metadata. Where the copies cover that, k_load_main is faster with its
+// registers and schedule than with the other form's: 77 blocks of 64 chunks of
+// 16 KiB (1 KiB of metadata) 35.0 us against 35.9, 300 of them 121.1 and 123.2,
+// 64 blocks of 128 chunks 52.4 and 54.2. The workgroup must be this one
+// wavefront: the tile barriers are workgroup barriers.
+__device__ __forceinline__ void load_meta_simple(const MetaArgs& a, uint32_t b, uint32_t lane, uint64_t* tile64) {
+  MetaCheck c;
+  uint32_t code = meta_begin(a, b, lane, c);
+  if (code) {
+    if (lane == 0) atomicOr(&a.status[b], code);
+    return;
+  }
+  uint64_t stored_root = 0;
+  uint64_t acc = root_init(lane);
+  const uint32_t* tile32 = (const uint32_t*)tile64;
+  for (uint32_t off = 0; off < c.meta; off += kMetaTile) {
+    const uint32_t nb = min(c.meta - off, kMetaTile);
+    const v4u* s = (const v4u*)(c.rec + off);
+    v4u* t4 = (v4u*)tile64;
+    for (uint32_t i = lane; i < nb / 16; i += 64) t4[i] = s[i];
+    __syncthreads();
+    if (off == 0) stored_root = tile64[tl::kRootOffset / 8];
+    for (uint32_t wd = lane; wd < nb / 4; wd += 64) {
+      const uint32_t o = off + 4 * wd;
+      const uint32_t x = tile32[wd];
+      if (o < tl::kHeaderBytes) {
+        if (o == tl::kIndexOffset) c.pos_bad |= x != (uint32_t)c.bi;
+        else if (o == tl::kIndexOffset + 4) c.pos_bad |= x != (uint32_t)(c.bi >> 32);
+        else if (o >= tl::kKeyOffset && o < tl::kKeyOffset + 32) c.key_bad |= x != c.key32[(o - tl::kKeyOffset) / 4];
+        else if (o == tl::kRootOffset || o == tl::kRootOffset + 4) {}
+        else if (o == tl::kTailOffset) c.hdr_bad |= x != (c.tk < a.g.block_tokens ? c.tk : 0);
+        else c.hdr_bad |= x != a.tmpl[o / 4];
+      } else if (o < a.g.tok_off) {
+        // chunk digests: checked by the chunk items, covered by the root
+      } else if (o < a.g.tok_end) {
+        const uint32_t wi = (o - a.g.tok_off) / 4;
+        if (wi >= c.tk) c.hdr_bad |= x != 0;  // the padding after a partial block's tokens
+        else if (c.tok) c.tok_bad |= x != c.tok[wi];
+      } else {
+        c.hdr_bad |= x != 0;
+      }
+    }
+    if (lane < 4) {
+      for (uint32_t st = 0; st < nb / 32; ++st) {
+        uint64_t x = tile64[st * 4 + lane];
+        if (off + st * 32 + lane * 8 == tl::kRootOffset) x = 0;  // the root reads as zero
+        acc = xx_round<false>(acc, x);
+      }
+    }
+    __syncthreads();
+  }
+  code = meta_end(a, c, acc, stored_root);
+  if (lane == 0 && code) atomicOr(&a.status[b], code);
+}
+
+// The form for loads that wait for a block's checks, staging through `tile64`
+// (kLoadTile bytes of LDS, this wavefront's own); returns the code. It is a chain
+// of memory waits and of the root's rounds, 35 ns per 32 bytes: 8 blocks of 400
+// chunks (5 KB of metadata, 1 KiB chunks) 14.7 us and 26.3 with the simple form,
+// one block of 550 pages (563 KB) 1,690 and 2,250.
+__device__ __forceinline__ uint32_t load_meta_chain(const MetaArgs& a, uint32_t b, uint32_t lane, uint64_t* tile64) {
+  MetaCheck c;
+  const uint32_t code = meta_begin(a, b, lane, c);
+  if (code) return code;
+  uint64_t stored_root = 0;
+  uint64_t acc = root_init(lane);
+  // A granule and the words it has to hold are loaded together and without
+  // branches, so that a tile costs one wait for memory; the next tile's are on
+  // their way while this one is hashed.
+  constexpr uint32_t kPer = kLoadTile / (16 * 64);
+  v4u x[kPer], want[kPer];
+  auto fetch = [&](uint32_t off) {
+#pragma unroll
+    for (uint32_t i = 0; i < kPer; ++i) {
+      const uint32_t o = off + 16 * (lane + 64 * i);
+      if (o >= c.meta) continue;
+      x[i] = *(const v4u*)(c.rec + o);
+      if (c.tok && o + 16 > a.g.tok_off) {
+#pragma unroll
+        for (uint32_t j = 0; j < 4; ++j) {
+          const uint32_t q = max(o + 4 * j, a.g.tok_off);
+          want[i][j] = c.tok[min((q - a.g.tok_off) / 4, a.g.block_tokens - 1)];
+        }
+      }
+    }
+  };
+  fetch(0);
+  v4u head;  // lanes 0-15: the header granule that the record has to hold
+  {
+    const uint32_t w0 = 4 * (lane & 15), key0 = tl::kKeyOffset / 4;
+#pragma unroll
+    for (uint32_t j = 0; j < 4; ++j) {
+      const uint32_t t = a.tmpl[w0 + j], k = c.key32[(w0 + j - key0) & 7];
+      head[j] = w0 + j - key0 < 8 ? k : t;
+    }
+    if (w0 == tl::kIndexOffset / 4) {  // (the granule's other half is the key's)
+      head.x = (uint32_t)c.bi;
+      head.y = (uint32_t)(c.bi >> 32);
+    }
+    if (w0 == tl::kRootOffset / 4) head.w = c.tk < a.g.block_tokens ? c.tk : 0;  // the root is zero in the template
+  }
+  for (uint32_t off = 0; off < c.meta; off += kLoadTile) {
+#pragma unroll
+    for (uint32_t i = 0; i < kPer; ++i) {
+      const uint32_t at = lane + 64 * i, o = off + 16 * at;
+      if (o >= c.meta) continue;
+      if (o == tl::kRootOffset) {  // reads as zero
+        stored_root = lo64(x[i]);
+        x[i].x = x[i].y = 0;
+      }
+      if (o < tl::kHeaderBytes) {
+#pragma unroll
+        for (uint32_t j = 0; j < 4; ++j) {
+          const uint32_t q = o + 4 * j;
+          const bool bad = x[i][j] != head[j], pos = q - tl::kIndexOffset < 8, key = q - tl::kKeyOffset < 32;
+          c.pos_bad |= bad & pos;
+          c.key_bad |= bad & key;
+          c.hdr_bad |= bad & !pos & !key;
+        }
+      } else if (o + 16 > a.g.tok_off) {
+        // (chunk digests before the token ids: checked by the chunk items,
+        // covered by the root)
+#pragma unroll
+        for (uint32_t j = 0; j < 4; ++j) {
+          const uint32_t q = o + 4 * j, v = x[i][j];
+          const bool ids = q < a.g.tok_end && (q - a.g.tok_off) / 4 < c.tk;
+          c.hdr_bad |= q >= a.g.tok_off & !ids & v != 0;  // padding, also after a partial block's tokens
+          c.tok_bad |= q >= a.g.tok_off & ids & c.tok != nullptr & v != want[i][j];
+        }
+      }
+      tile64[2 * at] = lo64(x[i]) * kP2;
+      tile64[2 * at + 1] = hi64(x[i]) * kP2;
+    }
+    wave_sync();
+    if (off + kLoadTile < c.meta) fetch(off + kLoadTile);
+    hash_tile(tile64, min(c.meta - off, kLoadTile), lane, acc);
+    wave_sync();
+  }
+  static_assert(tl::kIndexOffset % 16 == 0 && tl::kKeyOffset == tl::kIndexOffset + 8 && tl::kRootOffset % 16 == 0 &&
+                    tl::kTailOffset == tl::kRootOffset + 12, "the header's granules are as the checks take them");
+  stored_root = readlane64(stored_root, tl::kRootOffset / 16);
+  return meta_end(a, c, acc, stored_root);
+}
+
+// Chunk item w: copies the chunk to its page, digests it on the way and compares
+// with the stored digest; lane 0 calls `differs` with the item if it differs.
+// Records with a bad pointer or length are never read, and pages out of range
+// (-1: not restored) never written. Those exits are short on purpose: most items
+// of a hybrid model's load take them (65,536 blocks of 16 chunks, all refused:
+// 618 us, 664 with the comparison on every lane).
+template <int B, int PF, typename F>
+__device__ __forceinline__ void load_chunk(const SegArgs& a, uint32_t w, uint32_t lane, F&& differs) {
+  const Item it = decode(a, w);
+  if (!page_in_range(it.page, a.n_pages)) return;
   const uint64_t rec = a.rec[it.b];
-  if (rec == 0 || (rec & 15) || a.len[it.b] != a.g.record_bytes) return true;
-  const uint64_t leaf = copy_hash<B, PF>(record_chunk(a, rec, it), page_chunk(a, it), it.rows, lane);
+  if (rec == 0 || (rec & 15) || a.len[it.b] != a.g.record_bytes) return;
+  const uint64_t leaf = copy_hash<B, PF, false>(record_chunk(a, rec, it), page_chunk(a, it), it.rows, lane);
   const uint64_t digest = wave_sum64(leaf);
-  const uint64_t want = *(const uint64_t*)(rec + tl::kHeaderBytes + 8ull * it.t);
-  return want == digest || (a.disabled & TL_CHECK_SEGMENT);
+  if (lane == 0) {
+    const uint64_t want = *(const uint64_t*)(rec + tl::kHeaderBytes + 8ull * it.t);
+    if (want != digest && !(a.disabled & TL_CHECK_SEGMENT)) differs(it);
+  }
 }
 
 struct LoadArgs {
@@ -874,25 +965,31 @@ struct LoadArgs {
 
 // Items [0, n) are metadata items, [n, n + n * chunks) chunk items; one
 // wavefront per workgroup.
-template <int B, int PF>
-__device__ __forceinline__ void load_items(const LoadArgs& a, uint64_t* tile64) {
+template <int B, int PF, typename F>
+__device__ __forceinline__ void load_items(const LoadArgs& a, F&& meta_item) {
   const uint32_t lane = threadIdx.x;
   const uint32_t n_meta = a.s.n;
   const uint32_t total = n_meta + a.s.total;
   for (uint32_t w = blockIdx.x; w < total; w += gridDim.x) {
-    if (w < n_meta) {
-      const uint32_t code = load_meta_item(a.m, w, lane, tile64);
-      if (code && lane == 0) atomicOr(&a.s.status[w], code);
-    } else {
-      const Item it = decode(a.s, w - n_meta);
-      if (!load_chunk<B, PF>(a.s, it, lane) && lane == 0) atomicOr(&a.s.status[it.b], kSegFailBit);
-    }
+    if (w < n_meta)
+      meta_item(w, lane);
+    else
+      load_chunk<B, PF>(a.s, w - n_meta, lane, [&](const Item& it) { atomicOr(&a.s.status[it.b], kSegFailBit); });
   }
 }
 
 __global__ __launch_bounds__(64) void k_load_main(LoadArgs a) {
+  __shared__ uint64_t tile64[kMetaTile / 8];
+  load_items<TL_BATCH_ROWS, TL_PREFETCH>(a, [&](uint32_t b, uint32_t lane) { load_meta_simple(a.m, b, lane, tile64); });
+}
+
+// Loads that wait for their metadata items (meta_bound).
+__global__ __launch_bounds__(64) void k_load_main_meta(LoadArgs a) {
   __shared__ uint64_t tile64[kLoadTile / 8];
-  load_items<TL_BATCH_ROWS, TL_PREFETCH>(a, tile64);
+  load_items<TL_BATCH_ROWS, TL_PREFETCH>(a, [&](uint32_t b, uint32_t lane) {
+    const uint32_t code = load_meta_chain(a.m, b, lane, tile64);
+    if (code && lane == 0) atomicOr(&a.m.status[b], code);
+  });
 }
 
 // Slabs of several chunks: each wavefront has its whole 64 KiB chunk in flight
@@ -903,7 +1000,10 @@ __global__ __launch_bounds__(64) void k_load_main(LoadArgs a) {
 // (500 blocks of 120 64 KiB slabs 1,539 and 1,546 us, 32 KiB slabs 417 and 417).
 __global__ __launch_bounds__(64) void k_load_main_deep(LoadArgs a) {
   __shared__ uint64_t tile64[kLoadTile / 8];
-  load_items<64, 0>(a, tile64);
+  load_items<64, 0>(a, [&](uint32_t b, uint32_t lane) {
+    const uint32_t code = load_meta_chain(a.m, b, lane, tile64);
+    if (code && lane == 0) atomicOr(&a.m.status[b], code);
+  });
 }
 
 // A load of small blocks in one launch: a workgroup per block, whose first
@@ -925,9 +1025,9 @@ __global__ __launch_bounds__(1024) void k_load_block(LoadArgs a, uint8_t* verdic
   const uint32_t item = b * a.s.g.n_seg + wave - 1;  // of wavefronts 1..n_seg
   uint32_t st = 0;
   if (wave == 0) {
-    st = load_meta_item(a.m, b, lane, tile64);
-  } else if (!load_chunk<16, 0>(a.s, decode(a.s, item), lane)) {
-    st = kSegFailBit;
+    st = load_meta_chain(a.m, b, lane, tile64);
+  } else {
+    load_chunk<16, 0>(a.s, item, lane, [&](const Item&) { st = kSegFailBit; });
   }
   if (lane == 0) status[wave] = st;
   __syncthreads();
@@ -1227,6 +1327,19 @@ int launch_save(const tl_ctx* ctx, void* stream, size_t n, const tl_cache* src,
   return launch_save_seal(ctx, stream, n, src->n_pages, blk, d_rec, d_status);
 }
 
+// Whether a load of n blocks waits for its metadata items rather than for its
+// copies: load_meta_simple takes 100 ns per 32 bytes, all blocks at the same
+// time, against 5.2 TB/s of copying and at least 1.6 ns per chunk. With the
+// simple form and the other, by the ratio of copies to checks: 0.7 (4 blocks of
+// 128 chunks of 16 KiB) 13.8 and 11.8 us, 0.9 (one of 960 of 64 KiB) 34.2 and
+// 29.7, 1.9 (2 of 6,000) 311.0 and 312.8, 2.6 (64 of 400 of 1 KiB) 42.1 and 42.6,
+// 6.4 (16 of 256 of 32 KiB) 55.7 and 56.4.
+bool meta_bound(const Geo& g, size_t n) {
+  const uint64_t chain_ns = g.payload_offset * 100 / 32;
+  const uint64_t copy_ns = std::max(n * g.n_slabs * g.slab_bytes / 2600, n * (uint64_t)g.n_seg * 8 / 5);
+  return copy_ns <= 2 * chain_ns;
+}
+
 int launch_load(const tl_ctx* ctx, void* stream, size_t n, const uint64_t* d_rec,
                 const uint64_t* d_len, const tl_blocks* blk, const tl_cache* dst,
                 uint8_t* d_verdicts, uint32_t* d_ws) {
@@ -1264,6 +1377,8 @@ int launch_load(const tl_ctx* ctx, void* stream, size_t n, const uint64_t* d_rec
     const dim3 grid(n_items < (1u << 22) ? n_items : (1u << 22));
     if (ctx->geo.cps > 1)
       hipLaunchKernelGGL(k_load_main_deep, grid, dim3(64), 0, s, la);
+    else if (meta_bound(ctx->geo, n))
+      hipLaunchKernelGGL(k_load_main_meta, grid, dim3(64), 0, s, la);
     else
       hipLaunchKernelGGL(k_load_main, grid, dim3(64), 0, s, la);
   });

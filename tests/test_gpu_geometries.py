@@ -171,3 +171,34 @@ def test_ragged_chunks_of_small_and_large_blocks(layers, rows):
     hk0, hv0 = host_layers(dst)
     vo = check_restore(c, [bytes(r) for r in recs], store2.ptrs, store2.lens, t_dst, dst, hk0, hv0)
     assert vo == [ref.ACCEPT, ref.SEGMENT, ref.ACCEPT, ref.ACCEPT, ref.ACCEPT]
+
+
+# Metadata of several tiles (9,984 bytes, the token ids from 5,056 on), which a
+# load of 5 blocks waits for and one of 80 does not: the two forms of the checks
+# stage it 1 KiB and 4 KiB at a time. Flips on both sides of tile boundaries,
+# with the stored root and with one that fits them.
+@pytest.mark.parametrize("n", [5, 80])
+@pytest.mark.parametrize("offs,reroot", [((1023, 1024, 4095, 4096), False), ((5056, 8191, 8192, 9855), True),
+                                         ((9856, 9983, 5055, 6145), True)])
+def test_metadata_of_several_tiles(n, offs, reroot):
+    geom = wl.Geometry(2, 1, 64, 8, pages_per_block=150)
+    c = Case(geom, n, n * 150, n * 150 + 3, seed=37)
+    lay = c.lay
+    assert (ref.HEADER_BYTES + 8 * lay.n_segments, lay.payload_offset) == (5056, 9984)
+    c.make_src()
+    store, st = c.save()
+    assert (st == ref.ACCEPT).all()
+    recs = [bytearray(r.tobytes()) for r in store.buf.cpu().numpy()]
+    for b, o in enumerate(offs):
+        recs[b][o] ^= 0x04
+        if reroot:
+            recs[b][144:152] = ref.root_digest(bytes(recs[b][:144]) + bytes(8) + bytes(recs[b][152:9984])).to_bytes(8, "little")
+    store2 = upload_records(recs, lay.record_bytes)
+    dst = random_fill(PagedCache(geom.n_layers, n * 150 + 3, c.stride, DEV), 3)
+    hk0, hv0 = host_layers(dst)
+    log("metadata of several tiles", n, "blocks, flips at", offs)
+    vo = check_restore(c, [bytes(r) for r in recs], store2.ptrs, store2.lens, c.t_dst, dst, hk0, hv0)
+    want = [ref.ROOT] * 4
+    if reroot:  # token ids, padding, a chunk digest
+        want = [ref.TOKENS if 5056 <= o < 9856 else ref.HEADER if o >= 9856 else ref.SEGMENT for o in offs]
+    assert vo[:4] == want and set(vo[4:]) == {ref.ACCEPT}

@@ -81,17 +81,20 @@ GEOMS = {
     "hybrid": (wl.hybrid_geometry(n_layers=6, n_kv_heads=2, head_dim=64, page_tokens=16, window=32), 0),
     "multi_page": (wl.Geometry(2, 2, 64, 16, pages_per_block=3), 0),
     "multi_page_hybrid": (wl.Geometry(6, 2, 64, 16, "bf16", (32, 32, 32, 32, 32, 0), (1, 1, 1, 1, 1, 0), 2), 0),
+    # more chunks than a workgroup restores by itself; few blocks wait for their
+    # metadata checks (k_load_main_meta), many for their copies (k_load_main)
+    "rows1_16_chunks": (wl.Geometry(8, 1, 32, 16), 0),
+    "hybrid_24_chunks": (wl.hybrid_geometry(n_layers=12, n_kv_heads=2, head_dim=64, page_tokens=8, window=16), 48),
 }
 
 
-@pytest.mark.parametrize("name", list(GEOMS))
-def test_fault_zoo(name):
+@pytest.mark.parametrize("name,n", [(name, 26) for name in GEOMS] + [("rows1_16_chunks", 300), ("hybrid_24_chunks", 200)])
+def test_fault_zoo(name, n):
     geom, extra = GEOMS[name]
-    n = 26
     ppb = geom.pages_per_block
     cols = lambda b: slice(b * ppb, (b + 1) * ppb)  # table entries of block b
-    c = Case(geom, n, 40 * ppb, 48 * ppb, seed=11, stride_extra=extra)
-    log("fault zoo", name, "slab", c.lay.slab_bytes, "record", c.lay.record_bytes)
+    c = Case(geom, n, (n + 14) * ppb, (n + 22) * ppb, seed=11, stride_extra=extra)
+    log("fault zoo", name, n, "blocks, slab", c.lay.slab_bytes, "record", c.lay.record_bytes)
     c.make_src()
     store, st = c.save()
     recs_o, st_o = c.oracle_save()
