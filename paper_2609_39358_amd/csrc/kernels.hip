@@ -1049,13 +1049,25 @@ struct FinalArgs {
 // Verdicts, and zeros over the pages of rejected blocks (some of which
 // k_load_main may have written). Blocks go in tiles of 1,024; each of the
 // `parts` workgroups of a tile reads all of its status words, lists the
-// rejected blocks and zero-fills its share of their chunks, one per wavefront,
-// so that one rejected block already spreads over the device. Three rejected
-// blocks of 3,031 (60 layers, 64 KiB slabs): 11 us against 43 with a workgroup
-// per 64 chunks of every block, whose wavefronts zeroed 16 chunks one after
-// another; about 120 rejected blocks of 2 MiB 60 against 70.
+// rejected blocks and zero-fills a contiguous share of their chunks, so that
+// one rejected block spreads over all of them. Three rejected blocks of 3,031
+// (60 layers, 64 KiB slabs): 10.4 us against 45 with a workgroup per 64 chunks of
+// every block, whose wavefronts zeroed 16 chunks one after another.
 constexpr uint32_t kFinalTile = 1024;
-constexpr uint32_t kFinalWgs = 512;  // about as many workgroups in all
+
+// Workgroups per tile of `items` chunks: one per 64 chunks, which is enough where
+// all of its blocks are rejected, but about 512 in all, so that a single one
+// spreads over the device, and no more than 256 (1,024 wavefronts, enough for a
+// run of rejected blocks that lies in one tile) or 2,048 in all, since every one
+// of them reads the status words. 65,536 blocks of 16 chunks of 1 KiB: with 512
+// workgroups over all tiles 1,024 rejected blocks in a row took the load from
+// 1,740 to 1,955 us, and all of them rejected took this kernel 323 us; with
+// these 1,755 and 1,740, and 207 us. None rejected: 6 us and 23 (48 with a
+// workgroup per block).
+uint32_t final_parts(uint64_t items, uint32_t tiles) {
+  const uint64_t per_64 = std::min<uint64_t>(items / 64, std::max(2048 / tiles, 256u));
+  return (uint32_t)std::min<uint64_t>(std::max<uint64_t>(per_64, std::max(512 / tiles, 1u)), (items + 3) / 4);
+}
 
 __global__ __launch_bounds__(256) void k_load_final(FinalArgs f) {
   __shared__ uint32_t rejected[kFinalTile];  // in block order: every workgroup of a tile has the same list
@@ -1090,7 +1102,8 @@ __global__ __launch_bounds__(256) void k_load_final(FinalArgs f) {
   if (count == 0) return;
   __syncthreads();
   const uint32_t items = count * a.g.n_seg;
-  for (uint32_t w = part * 4 + uniform(tid >> 6); w < items; w += f.parts * 4) {
+  const uint32_t share = (items + f.parts - 1) / f.parts, end = min(items, (part + 1) * share);
+  for (uint32_t w = part * share + uniform(tid >> 6); w < end; w += 4) {
     const uint32_t q = w / a.g.n_seg;
     const Item it = decode(a, uniform(rejected[q]) * a.g.n_seg + (w - q * a.g.n_seg));
     if (!page_in_range(it.page, a.n_pages)) continue;
@@ -1354,8 +1367,7 @@ int launch_load(const tl_ctx* ctx, void* stream, size_t n, const uint64_t* d_rec
   f.s.order = 0;
   f.verdicts = d_verdicts;
   const uint32_t tiles = (uint32_t)((n + kFinalTile - 1) / kFinalTile);
-  const uint64_t tile_items = (uint64_t)std::min<size_t>(n, kFinalTile) * ctx->geo.n_seg;
-  f.parts = (uint32_t)std::min<uint64_t>(std::max(kFinalWgs / tiles, 1u), (tile_items + 3) / 4);
+  f.parts = final_parts((uint64_t)std::min<size_t>(n, kFinalTile) * ctx->geo.n_seg, tiles);
   const uint32_t n_items = (uint32_t)n + la.s.total;
   (void)hipGetLastError();
   if (ctx->geo.n_seg <= kBlockChunks) {

@@ -133,7 +133,8 @@ def test_long_digest_tables(layers, ppb, n, odd):
 # blocks at its edges, and with every block rejected.
 @pytest.mark.parametrize("layers,n,bad", [(7, 3, [0]), (8, 1, [0]), (8, 1023, [0, 1022]), (8, 1024, [1023]),
                                           (8, 1025, [1023, 1024]), (7, 1025, [0, 1024]),
-                                          (8, 2100, [0, 255, 256, 1024, 2047, 2048, 2099]), (8, 1100, range(1100))])
+                                          (8, 2100, [0, 255, 256, 1024, 2047, 2048, 2099]), (8, 1100, range(1100)),
+                                          (8, 3500, [3, *range(1024, 2048), *range(2050, 2173), 3499])])
 def test_rejected_blocks_at_tile_edges(layers, n, bad):
     geom = wl.Geometry(layers, 1, 64, 8)
     c = Case(geom, n, n, n + 3, seed=29)
