@@ -1009,12 +1009,10 @@ __global__ __launch_bounds__(64) void k_load_main_deep(LoadArgs a) {
 // A load of small blocks in one launch: a workgroup per block, whose first
 // wavefront checks the metadata while the others copy a chunk each; the verdict
 // comes after a barrier, and a rejected block is zeroed by the wavefronts that
-// copied it. The status words are in LDS. What such a load costs is its
-// launches: 64 blocks of 8 chunks of 8 KiB 13.5 us against 19.2 with the three
-// kernels, 1,000 blocks 28.2 and 35.5, 4,096 blocks 104 and 118; 14 chunks of
-// 13 KiB, 40 blocks 14.2 and 18.8, 2,000 blocks 149 and 154. A wavefront copies
-// one chunk: with 32 of 8 KiB per block, two or three each, 77 blocks took 40.0
-// us and 37.0 with the three kernels, with 64 of 16 KiB 54.0 and 35.5.
+// copied it. The status words are in LDS. What a small load costs is its
+// launches (64 blocks of 8 chunks of 8 KiB 7.5 us against 11.9 with the three
+// kernels), and a large one gains too (4,096 of 1 KiB chunks 46 and 67, 2,048 of
+// 14 chunks of 32 KiB 355 and 371). Which loads take it: block_kernel.
 constexpr uint32_t kBlockChunks = 15;  // of 16 wavefronts, one checks the metadata
 
 __global__ __launch_bounds__(1024) void k_load_block(LoadArgs a, uint8_t* verdicts, uint32_t b0) {
@@ -1353,6 +1351,19 @@ bool meta_bound(const Geo& g, size_t n) {
   return copy_ns <= 2 * chain_ns;
 }
 
+// Whether a load takes k_load_block. With a workgroup per block fewer blocks than
+// the 256 compute units leave some idle, which shows where a block takes its
+// compute unit long. Three kernels against one (chunks of the block): 8 and 64
+// blocks of 14 of 64 KiB 13.1 and 23.9, 28.2 and 44.1 us, 64 of 8 of 32 KiB 13.3
+// and 14.5, 64 of 14 of 16 KiB 13.3 and 13.8; but 256 of 14 of 64 KiB 96.5 and
+// 90.2, 32 of 8 of 32 KiB 12.8 and 11.2, 64 of 12 of 16 KiB 12.7 and 11.8. Up to
+// 4 chunks it is faster with any number of blocks: 64 of 4 of 64 KiB 15.2 and
+// 14.4, 128 19.3 and 17.7.
+bool block_kernel(const Geo& g, size_t n) {
+  const uint64_t most = n >= 256 ? ~0ull : n > 32 ? 192 << 10 : 256 << 10;  // bytes of a block
+  return g.n_seg <= 4 || (g.n_seg <= kBlockChunks && g.n_slabs * g.slab_bytes <= most);
+}
+
 int launch_load(const tl_ctx* ctx, void* stream, size_t n, const uint64_t* d_rec,
                 const uint64_t* d_len, const tl_blocks* blk, const tl_cache* dst,
                 uint8_t* d_verdicts, uint32_t* d_ws) {
@@ -1370,7 +1381,7 @@ int launch_load(const tl_ctx* ctx, void* stream, size_t n, const uint64_t* d_rec
   f.parts = final_parts((uint64_t)std::min<size_t>(n, kFinalTile) * ctx->geo.n_seg, tiles);
   const uint32_t n_items = (uint32_t)n + la.s.total;
   (void)hipGetLastError();
-  if (ctx->geo.n_seg <= kBlockChunks) {
+  if (block_kernel(ctx->geo, n)) {
     la.s.order = 0;
     constexpr size_t kGrid = 1u << 20;  // workgroups: a grid has fewer than 2^32 threads
     for (size_t b0 = 0; b0 < n; b0 += kGrid) {

@@ -127,8 +127,8 @@ def test_long_digest_tables(layers, ppb, n, odd):
             assert st[b] == T.MISSING and (got[b] == 0xA5).all(), b
 
 
-# Blocks of at most 15 chunks are restored by one workgroup each (7 layers: 14
-# chunks), longer ones by the whole grid (8 layers: 16), whose pass over
+# Small blocks of at most 15 chunks are restored by one workgroup each (7 layers:
+# 14 chunks), longer ones by the whole grid (8 layers: 16), whose pass over
 # verdicts takes 1,024 blocks at a time: counts around that, with rejected
 # blocks at its edges, and with every block rejected.
 @pytest.mark.parametrize("layers,n,bad", [(7, 3, [0]), (8, 1, [0]), (8, 1023, [0, 1022]), (8, 1024, [1023]),
@@ -151,10 +151,10 @@ def test_rejected_blocks_at_tile_edges(layers, n, bad):
     assert sorted(b for b in range(n) if vo[b] != ref.ACCEPT) == sorted(bad)
 
 
-# Slabs of a 64-row chunk and a ragged one, in blocks of 12 chunks (a workgroup
-# per block) and of 20 (whole chunks in flight), with pages that are not
-# restored (nor read) and damage in a chunk of one that is.
-@pytest.mark.parametrize("layers", [3, 5])
+# Slabs of a 64-row chunk and a ragged one, in blocks of 4 chunks (a workgroup
+# per block) and of 12 and 20, with pages that are not restored (nor read) and
+# damage in a chunk of one that is.
+@pytest.mark.parametrize("layers", [1, 3, 5])
 @pytest.mark.parametrize("rows", [65, 67, 96, 127])
 def test_ragged_chunks_of_small_and_large_blocks(layers, rows):
     geom = wl.Geometry(layers, 2, 256, rows)
@@ -172,6 +172,26 @@ def test_ragged_chunks_of_small_and_large_blocks(layers, rows):
     hk0, hv0 = host_layers(dst)
     vo = check_restore(c, [bytes(r) for r in recs], store2.ptrs, store2.lens, t_dst, dst, hk0, hv0)
     assert vo == [ref.ACCEPT, ref.SEGMENT, ref.ACCEPT, ref.ACCEPT, ref.ACCEPT]
+
+
+# Numbers and sizes of blocks on both sides of what one workgroup restores: 192
+# KiB with any number, 256 KiB up to 32 blocks, more from 256 blocks on.
+@pytest.mark.parametrize("rows,n", [(24, 33), (25, 32), (25, 33), (32, 32), (32, 33), (33, 32), (33, 255), (33, 256)])
+def test_blocks_around_one_workgroup(rows, n):
+    geom = wl.Geometry(4, 2, 256, rows)  # 8 chunks of `rows` KiB
+    c = Case(geom, n, n, n + 2, seed=33)
+    c.make_src()
+    store, _ = c.save()
+    recs = [bytearray(r.tobytes()) for r in store.buf.cpu().numpy()]
+    recs[0][c.lay.payload_offset + 5] ^= 1
+    recs[n - 2][80] ^= 0x40
+    recs[n - 1][-1] ^= 0x40
+    store2 = upload_records(recs, c.lay.record_bytes)
+    dst = random_fill(PagedCache(geom.n_layers, n + 2, c.stride, DEV), 3)
+    hk0, hv0 = host_layers(dst)
+    log("around one workgroup", c.lay.record_bytes, "bytes,", n, "blocks")
+    vo = check_restore(c, [bytes(r) for r in recs], store2.ptrs, store2.lens, c.t_dst, dst, hk0, hv0)
+    assert vo == [ref.SEGMENT] + [ref.ACCEPT] * (n - 3) + [ref.ROOT, ref.SEGMENT]
 
 
 # Metadata of several tiles (9,984 bytes, the token ids from 5,056 on), which a
