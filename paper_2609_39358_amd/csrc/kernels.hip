@@ -994,10 +994,18 @@ __global__ __launch_bounds__(64) void k_load_main_meta(LoadArgs a) {
 
 // Slabs of several chunks: each wavefront has its whole 64 KiB chunk in flight
 // before it stores. The chunks of such a page are written by neighbouring
-// wavefronts, and in one burst each they meet in memory: 48 layers of 1 MiB
-// slabs, 128 blocks 965 -> 902 us, 40 blocks 390 -> 370, 8 blocks 169 -> 163;
-// 96 KiB slabs, 1,500 blocks 1,414 -> 1,391. Slabs of one chunk gain nothing
-// (500 blocks of 120 64 KiB slabs 1,539 and 1,546 us, 32 KiB slabs 417 and 417).
+// wavefronts, and in one burst each they meet in memory. By how much it gains
+// depends on where the cache lies: 128 blocks of 48 layers of 1 MiB slabs 965 ->
+// 902 us in one process and 871 -> 836 in another, 8 blocks 318 -> 310; 1,000 of
+// 24 layers 65 KiB 1,344 -> 1,272, 96 KiB 1,882 -> 1,850, 128 KiB equal. Slabs of
+// one chunk gain nothing (500 blocks of 120 64 KiB slabs 1,539 and 1,546 us,
+// 32 KiB slabs 417 and 417). A SIMD holds one such wavefront and two of
+// k_load_main, and with few chunks for the device's 1,024 that shows: 25 blocks
+// of 96 chunks (65 KiB slabs) 46.0 -> 49.8 us, 50 76.9 -> 79.7, 25 of 96 KiB 55.5
+// -> 58.3; from 8 chunks per SIMD on (86 such blocks) it does not: 100 blocks
+// 141.9 -> 139.7, 256 of 32 chunks 122.6 -> 117.9. Hence kDeepItems.
+constexpr uint32_t kDeepItems = 8192;
+
 __global__ __launch_bounds__(64) void k_load_main_deep(LoadArgs a) {
   __shared__ uint64_t tile64[kLoadTile / 8];
   load_items<64, 0>(a, [&](uint32_t b, uint32_t lane) {
@@ -1398,7 +1406,7 @@ int launch_load(const tl_ctx* ctx, void* stream, size_t n, const uint64_t* d_rec
   });
   timed(TL_KERNEL_LOAD_MAIN, s, [&] {
     const dim3 grid(n_items < (1u << 22) ? n_items : (1u << 22));
-    if (ctx->geo.cps > 1)
+    if (ctx->geo.cps > 1 && la.s.total >= kDeepItems)
       hipLaunchKernelGGL(k_load_main_deep, grid, dim3(64), 0, s, la);
     else if (meta_bound(ctx->geo, n))
       hipLaunchKernelGGL(k_load_main_meta, grid, dim3(64), 0, s, la);

@@ -152,13 +152,13 @@ def test_rejected_blocks_at_tile_edges(layers, n, bad):
 
 
 # Slabs of a 64-row chunk and a ragged one, in blocks of 4 chunks (a workgroup
-# per block) and of 12 and 20, with pages that are not restored (nor read) and
-# damage in a chunk of one that is.
-@pytest.mark.parametrize("layers", [1, 3, 5])
-@pytest.mark.parametrize("rows", [65, 67, 96, 127])
-def test_ragged_chunks_of_small_and_large_blocks(layers, rows):
+# per block) and of 12 and 20, and of 1,024 of which 8 have 8,192 (whole chunks in
+# flight), with pages that are not restored (nor read) and damage in a chunk of
+# one that is.
+@pytest.mark.parametrize("layers,n,rows", [(layers, 5, rows) for layers in (1, 3, 5) for rows in (65, 67, 96, 127)] +
+                         [(256, 7, 65), (256, 8, 65), (256, 8, 79)])
+def test_ragged_chunks_of_small_and_large_blocks(layers, n, rows):
     geom = wl.Geometry(layers, 2, 256, rows)
-    n = 5
     c = Case(geom, n, n, n + 2, seed=31, stride_extra=48)
     c.make_src()
     store, _ = c.save()
@@ -171,7 +171,7 @@ def test_ragged_chunks_of_small_and_large_blocks(layers, rows):
     dst = random_fill(PagedCache(geom.n_layers, n + 2, c.stride, DEV), 3)
     hk0, hv0 = host_layers(dst)
     vo = check_restore(c, [bytes(r) for r in recs], store2.ptrs, store2.lens, t_dst, dst, hk0, hv0)
-    assert vo == [ref.ACCEPT, ref.SEGMENT, ref.ACCEPT, ref.ACCEPT, ref.ACCEPT]
+    assert vo == [ref.ACCEPT, ref.SEGMENT] + [ref.ACCEPT] * (n - 2)
 
 
 # Numbers and sizes of blocks on both sides of what one workgroup restores: 192
