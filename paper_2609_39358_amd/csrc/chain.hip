@@ -5,9 +5,9 @@
 // caller-supplied parent key (Sec. 2.2: state is stored under a fingerprint
 // of the exact input bytes, the model and the tenant; Sec. 5: reuse is of
 // whole blocks at exact positions). A chain is inherently sequential; the
-// chip's parallelism is across chains. Up to 16 chains per compute unit get a
-// workgroup of four wavefronts each (k_chain_waves), which divides the work of
-// one chain; beyond that chains share wavefronts, up to 64 (k_chain).
+// chip's parallelism is across chains. Few chains get a workgroup of four
+// wavefronts each (k_chain_waves), which divides the work of one chain; many
+// share wavefronts, up to 64 of them (k_chain; chain_waves draws the line).
 //
 // The walk probes the device index while it computes, so the lookup of key k
 // hides behind the hash of key k+1. Key k+1 is kept only once key k is known
@@ -32,10 +32,6 @@
 #include "internal.h"
 
 namespace {
-
-#ifndef TL_CHAIN_WAVES_PER_CU
-#define TL_CHAIN_WAVES_PER_CU 16  // chains per compute unit up to which each gets a workgroup
-#endif
 
 constexpr uint32_t kMaxProbe = 1024;  // slots a key may sit past its home slot
 constexpr uint32_t kNoSlot = 0xffffffffu;
@@ -1298,6 +1294,27 @@ ChainIn chain_in(const tl_ctx* ctx, size_t n_chains, const tl_chains* ch, uint32
 }
 }  // namespace
 
+// Whether each chain gets a workgroup (k_chain_waves) rather than a lane
+// (k_chain). A compute unit holds four such workgroups, and each of them begins
+// with a tile of schedules, so with many chains it takes work to be worth it.
+// Up to 8 chains per compute unit it always is: 2,048 chains of one key 16.7 us
+// and 16.4, of 2 28.4 and 42.7, of 65 0.70 ms and 1.66. Up to 16 with 8
+// compressions per chain that are sure to be made (a lookup may end at its second
+// key): 4,096 chains of 4 keys of 16 tokens (8 compressions) 92 us and 95, of 17
+// 354 and 433, of 2 of 64 tokens (looked up, none stored) 106 and 132; but of one
+// key 31.2 and 16.4 us, of 2 53.0 and 42.5, of 5 keys of 5 tokens 77.9 and 70.0,
+// 17 of 16 tokens looked up and none stored 65.3 and 56.1. Beyond that lanes are
+// faster: 8,192 chains of 64 blocks 2.47 ms and 1.46.
+bool chain_waves(const ChainIn& in, bool ends_early) {
+  const uint64_t cus = (uint64_t)sm_count();
+  if (in.n_chains <= 8 * cus) return true;
+  uint64_t keys = in.n_slots / in.n_chains;
+  if (ends_early) keys = std::min<uint64_t>(keys, 2);
+  // (slots may be more than there are tokens for: 16 of them to a compression, and one for the key)
+  const uint64_t work = std::min(keys * in.key.nb, in.n_tokens / in.n_chains / 16 + keys);
+  return in.n_chains <= 16 * cus && work >= 8;
+}
+
 int launch_chain(const tl_ctx* ctx, void* stream, size_t n_chains, const tl_chains* ch,
                  const void* index_mem, uint64_t capacity, uint32_t flags, uint8_t* d_keys,
                  uint64_t* d_handles, uint32_t* d_hits) {
@@ -1312,10 +1329,7 @@ int launch_chain(const tl_ctx* ctx, void* stream, size_t n_chains, const tl_chai
   a.hits = d_hits;
   a.lanes = 0;
   (void)hipGetLastError();
-  // A workgroup per chain while that is the faster way: 2,048 chains of 64
-  // blocks take 0.68 ms against 1.33 ms on lanes, 4,096 (16 per compute unit)
-  // 1.32 against 1.34, 8,192 2.47 against 1.46.
-  if (n_chains <= (uint64_t)TL_CHAIN_WAVES_PER_CU * sm_count()) {
+  if (chain_waves(a.in, index_mem && !a.all_keys)) {
     TimedLaunch t(TL_KERNEL_CHAIN, stream);
     hipLaunchKernelGGL(k_chain_waves, dim3((uint32_t)n_chains), dim3(256), 0, s, a);
   } else {

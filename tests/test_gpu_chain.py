@@ -307,29 +307,33 @@ def test_chain_lookup_equals_the_oracle_walk(capacity, flags):
 
 
 @pytest.mark.parametrize("page_tokens,ppb", [(5, 1), (16, 1), (24, 1), (16, 30)])
-@pytest.mark.parametrize("many", [False, True])
-def test_sequential_walk_at_the_edges_of_its_tiles(page_tokens, ppb, many):
+@pytest.mark.parametrize("extra,slots", [(0, 0), (2100, 0), (2100, 8), (4200, 0)])
+def test_sequential_walk_at_the_edges_of_its_tiles(page_tokens, ppb, extra, slots):
     """One, two, three and 31 compressions per block: a workgroup of four
     wavefronts walks a chain in tiles of 64 compressions with 16 keys between
-    its wavefronts; with thousands of chains a lane walks a chain. Chains end,
+    its wavefronts; with thousands of chains a lane walks a chain, from 2,049
+    on unless each has slots for some keys that are sure to be made. Chains end,
     and have their one block with no stored state, around those edges; keys
-    past the first missing one are written only with TL_CHAIN_ALL_KEYS."""
+    past the first missing one are written only with TL_CHAIN_ALL_KEYS. The
+    `extra` chains hold `slots` blocks each, none of them stored."""
     ctx, ns, bt = ctx_bt(page_tokens, ppb)
     edges = [0, 1, 2, 14, 15, 16, 17, 31, 32, 33, 62, 63, 64, 65]
     data = [wl.tokens((n + hole) * bt + 3, 50 * n + hole) for n in edges for hole in (0, 1)]
     holes = [n for n in edges for _ in (0, 1)]
     data += [wl.tokens(130 * bt + bt - 1, 7000 + h) for h in edges]
     holes += edges
-    lengths = [d.size for d in data] + [0] * (4200 if many else 0)
-    nk = [-(-L // bt) for L in lengths]
+    lengths = [d.size for d in data] + [slots * bt] * extra
+    nk = [-(-d.size // bt) for d in data] + [slots] * extra
     ch = Chains(ctx, lengths, 1, bt, slot_counts=nk)
-    ch.tokens = np.concatenate(data)
+    ch.tokens[:sum(d.size for d in data)] = np.concatenate(data)
     ch.d_tok.copy_(i32(ch.tokens.view(np.int32)))
     want = [ref.block_keys(ns, d.tobytes(), 4 * bt, tail=True) for d in data]
     idx = new_index(1 << 14)
     stored = [k for w, h in zip(want, holes) for i, k in enumerate(w) if i != h]
     assert (dput(idx, stored, np.arange(len(stored)) + 5) == T.TL_INDEX_STORED).all()
     handle = {k: i + 5 for i, k in enumerate(stored)}
+    few = range(len(data), ch.n, 97) if slots else []  # some of the extra chains
+    more = [ref.block_keys(ns, ch.data(c), 4 * bt) for c in few]
     for flags in (T.TL_CHAIN_TAIL, T.TL_CHAIN_TAIL | T.TL_CHAIN_ALL_KEYS):
         log("sequential walk: block tokens", bt, "chains", ch.n, "flags", flags)
         keys, handles, hits = ch.lookup(ctx, idx, flags)
@@ -340,8 +344,10 @@ def test_sequential_walk_at_the_edges_of_its_tiles(page_tokens, ppb, many):
             assert [keys[s0 + i].tobytes() for i in range(kept)] == w[:kept], (c, h)
             assert (keys[s0 + kept:s0 + len(w)] == SENT).all(), (c, h)
             assert handles[s0:s0 + len(w)].tolist() == [handle[k] for k in w[:n]] + [T.MISS] * (len(w) - n)
+        assert (hits[len(want):] == 0).all() and (handles[int(ch.slot_off[len(want)]):] == np.uint64(T.MISS)).all()
+        assert [keys[int(ch.slot_off[c])].tobytes() for c in few] == [w[0] for w in more]
     keys, _, hits = ch.lookup(ctx, None, T.TL_CHAIN_TAIL)
-    for c, w in enumerate(want):
+    for c, w in list(enumerate(want)) + list(zip(few, more)):
         s0 = int(ch.slot_off[c])
         assert hits[c] == len(w) and [keys[s0 + i].tobytes() for i in range(len(w))] == w, c
 
