@@ -251,10 +251,13 @@ __global__ __launch_bounds__(256) void k_dindex_publish(PutArgs a) {
 }
 
 // A put of at most kPutThreads keys in one launch: barriers stand where the
-// others have the ends of kernels. Blocks saved and indexed, two puts: 62 of a
-// small model 158 -> 145 us, 512 170 -> 158; 1,024 in one workgroup 197 against
-// 187 with three kernels on the whole device, hence the bound.
-constexpr uint32_t kPutThreads = 512;
+// others have the ends of kernels. One compute unit has to do it, which shows
+// with inserts, above all where keys sit far from their home slots. Keys new to
+// an index that is 45 % full (three kernels, one): 62 13.5 and 11.7 us, 256 16.7
+// and 16.1, 320 18.4 and 18.8, 512 17.8 and 21.9; to an empty one 256 9.3 and
+// 9.1, 320 9.5 and 10.3, 512 10.5 and 15.0; hence the bound. (Puts of keys that
+// are there already: 256 10.6 and 6.7, 512 10.9 and 10.1.)
+constexpr uint32_t kPutThreads = 256;
 
 __global__ __launch_bounds__(kPutThreads) void k_dindex_put(PutArgs a) {
   const uint32_t i = threadIdx.x;

@@ -230,7 +230,7 @@ def test_device_index_random_batches(seed):
         assert n_used == len(model) <= cap and 0 <= maxp < 1024
 
 
-@pytest.mark.parametrize("n", [1, 63, 64, 511, 512, 513])
+@pytest.mark.parametrize("n", [1, 63, 64, 255, 256, 257, 511, 512, 513])
 def test_device_index_put_sizes(n):
     """Puts around the size up to which one workgroup does all three phases:
     every key twice in the call, then half of them overwritten."""
