@@ -16,7 +16,8 @@
 //          k_save_meta (header, token ids, padding, root over the metadata;
 //                       long digest tables are hashed beside the copy, see
 //                       k_save_slice)
-//   load:  k_load_init (clear the per-block status words)
+//   load:  (small blocks: one kernel, k_load_block)
+//          k_load_init (clear the per-block status words)
 //          k_load_main (one grid: per block, pointer/length/root/header/
 //                       position/key/token checks; per chunk, record -> page
 //                       copy + chunk digest + compare)
@@ -601,9 +602,9 @@ __device__ __forceinline__ MetaWords meta_words(const MetaArgs& a, uint32_t b, u
 
 // Feeds metadata bytes [from, to) (multiples of 32) to the root's accumulators
 // (lanes 0-3 of the first wavefront), writing what the record does not hold
-// yet if `write`.
+// yet from byte `write` on.
 __device__ __forceinline__ void meta_hash(const MetaArgs& a, const MetaWords& m, uint64_t rec, uint32_t from, uint32_t to,
-                                          bool write, MetaTiles& tile, uint64_t& acc) {
+                                          uint32_t write, MetaTiles& tile, uint64_t& acc) {
   const uint32_t tid = threadIdx.x;
   auto stage = [&](uint32_t off, uint64_t* buf) {
     const uint32_t o = off + 16 * tid;
@@ -614,7 +615,7 @@ __device__ __forceinline__ void meta_hash(const MetaArgs& a, const MetaWords& m,
     } else {
       x = v4u{meta_word(a, m, rec, o), meta_word(a, m, rec, o + 4), meta_word(a, m, rec, o + 8),
               meta_word(a, m, rec, o + 12)};
-      if (write && o != tl::kRootOffset) *(v4u*)(rec + o) = x;
+      if (o >= write && o != tl::kRootOffset) *(v4u*)(rec + o) = x;
     }
     // the root field is zero in x (the template holds zeros there)
     buf[2 * tid] = ((uint64_t)x.y << 32 | x.x) * kP2;
@@ -637,10 +638,25 @@ __device__ __forceinline__ uint32_t meta_ready(const MetaArgs& a, uint32_t b, ui
   return done ? (tl::kHeaderBytes + 8 * done) & ~31u : 0;
 }
 
-// Finishes the metadata of every block. `hashed`: work items whose digests
-// k_save_slice has already hashed (0: none); the accumulators of a block it has
-// begun are in the record's first 32 bytes.
-__global__ __launch_bounds__(kMetaThreads) void k_save_meta(MetaArgs a, uint32_t hashed) {
+// Where the root's accumulators of a block wait between the launches of a save
+// in slices: in its record's header, which is written last. Several blocks of a
+// call may name one record (and then hold the same bytes), so what one writes
+// is either what every other would write there, or read by itself alone: the
+// state after all digests has a place, and the one block that a launch leaves
+// in between has one of two, by the launch's number.
+constexpr uint32_t kStateWhole = 0, kStatePart = 32, kStateBytes = 32;
+static_assert(kStatePart + 2 * kStateBytes <= tl::kRootOffset, "the root is written before the header");
+
+__device__ __forceinline__ uint64_t* state_of(const MetaArgs& a, uint64_t rec, uint32_t done, uint32_t launch) {
+  const bool whole = done == ((tl::kHeaderBytes + 8 * a.g.n_seg) & ~31u);
+  return (uint64_t*)(rec + (whole ? kStateWhole : kStatePart + (launch & 1) * kStateBytes));
+}
+
+// Finishes the metadata of every block. kSliced: `hashed` work items' digests are
+// hashed already by `launch` launches, and the header but for the root is left
+// to k_save_head.
+template <bool kSliced>
+__global__ __launch_bounds__(kMetaThreads) void k_save_meta(MetaArgs a, uint32_t hashed, uint32_t launch) {
   __shared__ MetaTiles tile;
   const uint32_t tid = threadIdx.x;
   const uint32_t lane = tid & 63;
@@ -661,26 +677,39 @@ __global__ __launch_bounds__(kMetaThreads) void k_save_meta(MetaArgs a, uint32_t
     return;
   }
   const MetaWords m = meta_words(a, b, tk);
-  const uint32_t from = meta_ready(a, b, hashed);
+  const uint32_t from = kSliced ? meta_ready(a, b, hashed) : 0;
   uint64_t acc = root_init(lane);
-  if (from) {
-    if (tid < 4) acc = *(const uint64_t*)(rec + 8 * tid);
-    __syncthreads();  // the accumulators are read before the header takes their place
-    const uint32_t o = 16 * tid;
-    if (o < tl::kHeaderBytes && o != tl::kRootOffset)
-      *(v4u*)(rec + o) = v4u{meta_word(a, m, rec, o), meta_word(a, m, rec, o + 4), meta_word(a, m, rec, o + 8),
-                             meta_word(a, m, rec, o + 12)};
-  }
-  meta_hash(a, m, rec, from, meta, true, tile, acc);
+  if (from && tid < 4) acc = state_of(a, rec, from, launch)[tid];
+  meta_hash(a, m, rec, from, meta, kSliced ? tl::kHeaderBytes : 0, tile, acc);
   if (tid < 64) {
     const uint64_t root = finish_root(acc, meta);
     if (tid == 0) {
-      // bytes 152..159: pages per block (from the expected header), then the tail field
-      *(v4u*)(rec + tl::kRootOffset) = v4u{(uint32_t)root, (uint32_t)(root >> 32),
-                                           a.tmpl[tl::kPpbOffset / 4], m.tail};
+      if (kSliced) {
+        *(uint64_t*)(rec + tl::kRootOffset) = root;
+      } else {
+        // bytes 152..159: pages per block (from the expected header), then the tail field
+        *(v4u*)(rec + tl::kRootOffset) = v4u{(uint32_t)root, (uint32_t)(root >> 32),
+                                             a.tmpl[tl::kPpbOffset / 4], m.tail};
+      }
       if (a.out_status) a.out_status[b] = TL_ACCEPT;
     }
   }
+}
+
+// Headers of a save in slices, without the root: one wavefront per block. A
+// launch of its own, since the accumulators lie there until every block has its
+// root.
+__global__ __launch_bounds__(64) void k_save_head(MetaArgs a) {
+  const uint32_t lane = threadIdx.x, b = blockIdx.x;
+  const uint64_t rec = a.rec[b];
+  const uint32_t tk = block_tok(a.g, a.n_tokens, b);
+  if (rec == 0 || (rec & 15) || tk == 0 ||
+      !block_pages_ok(a.g, a.tables, a.n, b, a.n_pages, 0, lane, pages_used(a.g, tk)))
+    return;
+  const MetaWords m = meta_words(a, b, tk);
+  const uint32_t o = 8 * lane;
+  if (o < tl::kHeaderBytes && o != tl::kRootOffset)
+    *(uint64_t*)(rec + o) = (uint64_t)meta_word(a, m, rec, o + 4) << 32 | meta_word(a, m, rec, o);
 }
 
 // A slice of a save whose records have long digest tables: workgroups
@@ -688,12 +717,16 @@ __global__ __launch_bounds__(kMetaThreads) void k_save_meta(MetaArgs a, uint32_t
 // completed, one block each from block b0 on, while the others copy the work
 // items [s.first, s.total). The root is one serial chain (35 ns per four
 // digests), 0.6 ms for a block of 550 pages; run after the copy it left the
-// device idle for that long (save_cuts says how the slices are sized).
+// device idle for that long (save_cuts says how the slices are sized). The
+// hashing workgroups come first and have the copy's footprint, one to a compute
+// unit, which costs nothing with many blocks either: 800 blocks of 8,192 chunks
+// of 1 KiB 22.45 ms with one launch and 22.31 so, 200 of 4 KiB 7.86 and 7.75.
 struct SliceArgs {
   SegArgs s;
   MetaArgs m;
   uint32_t b0, n_hash;
   uint32_t from_items, to_items;  // digests of work items [from_items, to_items)
+  uint32_t launch;                // number of this launch: its state's place
 };
 
 __global__ __launch_bounds__(64 * kSegWaves) void k_save_slice(SliceArgs a) {
@@ -712,9 +745,9 @@ __global__ __launch_bounds__(64 * kSegWaves) void k_save_slice(SliceArgs a) {
       !block_pages_ok(a.m.g, a.m.tables, a.m.n, b, a.m.n_pages, 0, lane, pages_used(a.m.g, tk)))
     return;
   uint64_t acc = root_init(lane);
-  if (from && tid < 4) acc = *(const uint64_t*)(rec + 8 * tid);
-  meta_hash(a.m, meta_words(a.m, b, tk), rec, from, to, false, tile, acc);
-  if (tid < 4) *(uint64_t*)(rec + 8 * tid) = acc;
+  if (from && tid < 4) acc = state_of(a.m, rec, from, a.launch - 1)[tid];
+  meta_hash(a.m, meta_words(a.m, b, tk), rec, from, to, ~0u, tile, acc);
+  if (tid < 4) state_of(a.m, rec, to, a.launch)[tid] = acc;
 }
 
 // ---- load ---------------------------------------------------------------------
@@ -1263,7 +1296,7 @@ int launch_save_seal(const tl_ctx* ctx, void* stream, size_t n, int64_t n_pages,
   fill_meta(m, ctx, n, d_rec, nullptr, blk, n_pages, nullptr, d_status);
   (void)hipGetLastError();
   timed(TL_KERNEL_SAVE_META, s, [&] {
-    hipLaunchKernelGGL(k_save_meta, dim3((uint32_t)n), dim3(kMetaThreads), 0, s, m, 0u);
+    hipLaunchKernelGGL(k_save_meta<false>, dim3((uint32_t)n), dim3(kMetaThreads), 0, s, m, 0u, 0u);
   });
   return launched();
 }
@@ -1306,7 +1339,8 @@ SaveCuts save_cuts(const Geo& g, size_t n) {
 }
 
 // A save in slices: launch i copies items [end[i-1], end[i]) and hashes the
-// digests that launch i-1 completed; k_save_meta hashes the rest.
+// digests that launch i-1 completed; k_save_meta hashes the rest and
+// k_save_head ends the records.
 int launch_save_sliced(const tl_ctx* ctx, hipStream_t s, size_t n, const tl_cache* src, const tl_blocks* blk,
                        const uint64_t* d_rec, uint8_t* d_status, const SaveCuts& cuts) {
   SliceArgs a;
@@ -1325,6 +1359,7 @@ int launch_save_sliced(const tl_ctx* ctx, hipStream_t s, size_t n, const tl_cach
       } else {
         a.b0 = a.from_items / a.m.g.n_seg;
         a.n_hash = (a.to_items - 1) / a.m.g.n_seg - a.b0 + 1;
+        a.launch = i;
         hipLaunchKernelGGL(k_save_slice, dim3(a.n_hash + grid), dim3(64 * kSegWaves), 0, s, a);
       }
     });
@@ -1332,7 +1367,8 @@ int launch_save_sliced(const tl_ctx* ctx, hipStream_t s, size_t n, const tl_cach
     a.to_items = end;
   }
   timed(TL_KERNEL_SAVE_META, s, [&] {
-    hipLaunchKernelGGL(k_save_meta, dim3((uint32_t)n), dim3(kMetaThreads), 0, s, a.m, a.from_items);
+    hipLaunchKernelGGL(k_save_meta<true>, dim3((uint32_t)n), dim3(kMetaThreads), 0, s, a.m, a.from_items, a.launch);
+    hipLaunchKernelGGL(k_save_head, dim3((uint32_t)n), dim3(64), 0, s, a.m);
   });
   return launched();
 }

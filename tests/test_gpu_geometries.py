@@ -127,6 +127,40 @@ def test_long_digest_tables(layers, ppb, n, odd):
             assert st[b] == T.MISSING and (got[b] == 0xA5).all(), b
 
 
+# A call may name one record several times, for the same block (requests of one
+# batch that share it): all of them write the same bytes. Records with long
+# digest tables are hashed while others of the call are copied: blocks of one
+# record that are whole by then, not begun, and in between.
+@pytest.mark.parametrize("ppb,same", [(2048, [0, 0]), (2048, [0, 1, 0, 1, 2]), (5000, [0, 0, 0]), (7001, [0, 1, 1, 0]),
+                                      (64, [0, 0, 1])])
+def test_blocks_of_one_record(ppb, same):
+    from paper_2609_39358_amd import taliesin as T
+    from paper_2609_39358_amd.device import RecordStore
+    from tests.gpu_case import i32
+    geom = wl.Geometry(2, 1, 64, 8, pages_per_block=ppb)
+    n = len(same)
+    c = Case(geom, n, n * ppb, n * ppb, seed=41, block_index=same)
+    c.make_src()
+    c.tokens = np.ascontiguousarray(c.tokens[same])
+    c.keys = np.ascontiguousarray(c.keys[same])
+    tables = np.concatenate([c.t_src[:, b * ppb:(b + 1) * ppb] for b in same], axis=1)
+    recs_o, st_o = ref.save(c.lay, c.ns, *host_layers(c.src), tables, [k.tobytes() for k in c.keys], c.bidx, c.tokens,
+                            n_pages=c.src_pages)
+    blk = T.make_blocks(torch.from_numpy(c.keys).to(DEV), c.d_bidx, i32(c.tokens.view(np.int32)), i32(tables))
+    store = RecordStore(n, c.lay.record_bytes, DEV)
+    ptrs = store.ptrs[torch.tensor(same, device=DEV)]
+    st = torch.zeros(n, dtype=torch.uint8, device=DEV)
+    log("blocks of one record", ppb, "pages,", same)
+    for seed in range(3):  # the records' bytes before the save change nothing
+        store.buf.random_(generator=torch.Generator(device=DEV).manual_seed(seed))
+        T.tl_save(c.ctx, torch.cuda.current_stream(), n, c.src.tl(), blk, ptrs, st)
+        torch.cuda.synchronize()
+        assert [int(x) for x in st.cpu()] == st_o == [ref.ACCEPT] * n
+        got = store.buf.cpu().numpy()
+        for b, r in enumerate(same):
+            assert got[r].tobytes() == recs_o[b], (b, r)
+
+
 # Small blocks of at most 15 chunks are restored by one workgroup each (7 layers:
 # 14 chunks), longer ones by the whole grid (8 layers: 16), whose pass over
 # verdicts takes 1,024 blocks at a time: counts around that, with rejected
