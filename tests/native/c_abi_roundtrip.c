@@ -1,15 +1,15 @@
 /* Save -> damage -> load through the C ABI alone (taliesin.h and the HIP
- * runtime; no Python, no torch): 32 blocks of a 4-layer model saved from a
- * paged cache, one payload byte of record 5 flipped in device memory, and
- * the records restored into a second cache through other page tables. Every
- * verdict must be ACCEPT except block 5 (SEGMENT), every restored page must
- * equal its source page, and block 5's pages must be zero; then the same
- * restore again through tl_load_static, which allocates nothing. Prints one
- * line and returns 0 on success. With a file name as its argument it also writes
- * its inputs and outputs there, back to back, for a check against the
- * oracle: the token ids, keys and both page tables, the source pages (per
- * layer, K then V), the records as saved, the verdicts, then the destination
- * pages after the load. */
+ * runtime; no Python, no torch): 32 blocks of a model of 4 layers (or as many
+ * as the second argument says, up to 8) saved from a paged cache, one payload
+ * byte of record 5 flipped in device memory, and the records restored into a
+ * second cache through other page tables. Every verdict must be ACCEPT except
+ * block 5 (SEGMENT), every restored page must equal its source page, and block
+ * 5's pages must be zero; then the same restore again through tl_load_static,
+ * which allocates nothing. Prints one line and returns 0 on success. With a file
+ * name as its first argument it also writes its inputs and outputs there, back
+ * to back, for a check against the oracle: the token ids, keys and both page
+ * tables, the source pages (per layer, K then V), the records as saved, the
+ * verdicts, then the destination pages after the load. */
 #include <hip/hip_runtime_api.h>
 #include <stdio.h>
 #include <stdlib.h>
@@ -99,8 +99,10 @@ static int check_restore(const uint8_t* verd, int nb, int n_layers, size_t slab,
 }
 
 int main(int argc, char** argv) {
-  enum { L = 4, NB = 32, PAGES = 40 };
-  tl_layout lay = {L, 4, 64, TL_DTYPE_BF16, 16, 1, NULL, NULL};
+  enum { MAX_L = 8, NB = 32, PAGES = 40 };
+  const int L = argc > 2 ? atoi(argv[2]) : 4; /* layers: 4 or 8 */
+  if (L < 1 || L > MAX_L) return 1;
+  tl_layout lay = {(uint32_t)L, 4, 64, TL_DTYPE_BF16, 16, 1, NULL, NULL};
   int st = 0;
   tl_ctx* ctx = tl_ctx_create("tenant-c", 8, "model-c", 7, &lay, &st);
   if (!ctx) {
@@ -112,7 +114,7 @@ int main(int argc, char** argv) {
   const size_t slab = g.slab_bytes, rb = g.record_bytes;
 
   /* source and destination caches: one allocation per layer and K/V */
-  uint64_t src_k[L], src_v[L], dst_k[L], dst_v[L];
+  uint64_t src_k[MAX_L] = {0}, src_v[MAX_L] = {0}, dst_k[MAX_L] = {0}, dst_v[MAX_L] = {0};
   uint8_t* host = (uint8_t*)malloc(PAGES * slab);
   for (int l = 0; l < L; ++l) {
     void* p;

@@ -15,14 +15,15 @@ from paper_2609_39358_amd import build as B
 
 pytestmark = pytest.mark.gpu
 
-L, NB, PAGES, P = 4, 32, 40, 16
+NB, PAGES, P = 32, 40, 16
 
 
-def test_c_abi_round_trip(tmp_path):
+@pytest.mark.parametrize("L", [4, 8])  # layers: loads in one kernel, in three
+def test_c_abi_round_trip(tmp_path, L):
     if not os.path.exists(B.C_ABI_TEST):
         pytest.fail("the C-ABI test program is not built (run __graft_entry__.build())")
     out = tmp_path / "dump.bin"
-    r = subprocess.run([B.C_ABI_TEST, str(out)], capture_output=True, text=True, timeout=120)
+    r = subprocess.run([B.C_ABI_TEST, str(out), str(L)], capture_output=True, text=True, timeout=120)
     print(r.stdout, r.stderr, flush=True)
     assert r.returncode == 0, r.stderr
     assert "round trip ok" in r.stdout

@@ -1,12 +1,13 @@
 """tl_load (and tl_load_static) under HIP graph capture, and tl_load on
 concurrent streams.
 
-The load issues three kernels and no memset, so a caller can capture it once
-and replay it: every replay below runs after eager work of the program itself
-(refilling the destination, changing record bytes and lengths in place) and is
-checked against an eager run on the same inputs. Two loads on two streams with
-separate workspaces must not disturb each other, and a workspace full of
-garbage must not matter."""
+The load issues one kernel (small blocks) or three and no memset, so a caller
+can capture it once and replay it: every replay below runs after eager work of
+the program itself (refilling the destination, changing record bytes and lengths
+in place) and is checked against an eager run on the same inputs. Two loads on
+two streams with separate workspaces must not disturb each other, and a
+workspace full of garbage must not matter. All of it for every kernel that a load
+of 24 blocks takes."""
 import numpy as np
 import pytest
 import torch
@@ -20,8 +21,15 @@ from tests.gpu_case import DEV, Case, host_layers, i32, i64, log, random_fill
 pytestmark = pytest.mark.gpu
 
 
-def _setup(seed=21):
-    geom = wl.Geometry(3, 4, 64, 16)
+GEOMS = {
+    "block": wl.Geometry(3, 4, 64, 16),  # 6 chunks: a workgroup per block, status words in LDS
+    "meta": wl.Geometry(8, 4, 64, 16),  # 16 of 8 KiB: three kernels, the checks waited for
+    "main": wl.Geometry(8, 16, 128, 16),  # 16 of 64 KiB: three kernels, the copies waited for
+    "deep": wl.Geometry(86, 2, 256, 65),  # 344 of 64 and 1 KiB: three kernels, whole chunks in flight
+}
+
+
+def _setup(geom, seed=21):
     c = Case(geom, 24, 32, 40, seed=seed)
     c.make_src()
     store, st = c.save()
@@ -29,13 +37,14 @@ def _setup(seed=21):
     return c, store
 
 
+@pytest.mark.parametrize("name", list(GEOMS))
 @pytest.mark.parametrize("static", [False, True])
-def test_captured_load_replays_match_eager(static):
+def test_captured_load_replays_match_eager(static, name):
     """static: capture tl_load_static (no workspace; the library's per-device
     status array), the entry point for callers that cannot allocate, against
     the same eager tl_load."""
     T.tl_timing(False)
-    c, store = _setup()
+    c, store = _setup(GEOMS[name])
     n = c.n
     lens = store.lens.clone()
     d_tab = i32(c.t_dst)
@@ -103,8 +112,9 @@ def test_captured_load_replays_match_eager(static):
     assert [int(x) for x in got_v][11] == ref.ROOT
 
 
-def test_two_loads_on_two_streams():
-    c, store = _setup(seed=22)
+@pytest.mark.parametrize("name", list(GEOMS))
+def test_two_loads_on_two_streams(name):
+    c, store = _setup(GEOMS[name], seed=22)
     n = c.n
     tabs = [c.t_dst, wl.page_table(n, c.dst_pages, 99, 0)[None, :]]
     dsts = [PagedCache(c.geom.n_layers, c.dst_pages, c.stride, DEV) for _ in range(2)]

@@ -16,6 +16,7 @@ from tests.gpu_case import DEV, FP, TEN, Case, ctx_of, fill_cache, host_layers, 
 
 pytestmark = pytest.mark.gpu
 
+LAYERS = [2, 8]  # blocks of 4 chunks (restored by one kernel) and of 16 (by three)
 SPIN = 40_000_000  # clock cycles of torch's bounded spin kernel (milliseconds)
 
 
@@ -25,8 +26,9 @@ def delayed(t: torch.Tensor) -> torch.Tensor:
     return t.clone()
 
 
-def test_host_pipeline_on_a_side_stream():
-    geom = wl.Geometry(2, 4, 64, 16)
+@pytest.mark.parametrize("layers", LAYERS)
+def test_host_pipeline_on_a_side_stream(layers):
+    geom = wl.Geometry(layers, 4, 64, 16)
     n, bt = 24, geom.block_tokens
     c = Case(geom, n, 32, 32, seed=41)
     c.make_src()
@@ -53,8 +55,9 @@ def test_host_pipeline_on_a_side_stream():
             assert torch.equal(dk[:20, :slab], want)
 
 
-def test_device_store_and_restore_on_a_side_stream():
-    geom = wl.Geometry(2, 4, 64, 16)
+@pytest.mark.parametrize("layers", LAYERS)
+def test_device_store_and_restore_on_a_side_stream(layers):
+    geom = wl.Geometry(layers, 4, 64, 16)
     ctx, lay = ctx_of(geom), layout_of(geom)
     ns, bt = ref.namespace_digest(TEN, FP, lay), geom.block_tokens
     store = pipeline.DeviceStore(ctx, 64, DEV)
@@ -96,8 +99,9 @@ def test_device_store_and_restore_on_a_side_stream():
             assert torch.equal(tb[:25], ta[:25]) and (tb[25:] == 0x42).all()
 
 
-def test_file_restore_on_a_side_stream(tmp_path):
-    geom = wl.Geometry(2, 4, 64, 16)
+@pytest.mark.parametrize("layers", LAYERS)
+def test_file_restore_on_a_side_stream(tmp_path, layers):
+    geom = wl.Geometry(layers, 4, 64, 16)
     n = 21
     c = Case(geom, n, 32, 32, seed=43)
     c.make_src()

@@ -56,11 +56,12 @@ def test_release_library_has_no_sabotage_entry_point():
     assert os.path.exists(B.SABOTAGE_OUT)
 
 
-def test_each_defence_on_off_restored():
+# a workgroup per block; three kernels, the checks or the copies waited for
+@pytest.mark.parametrize("layers,heads", [(2, 2), (8, 2), (16, 32)])
+def test_each_defence_on_off_restored(layers, heads):
     lib = sabotage_lib()
-    geom = wl.Geometry(2, 2, 64, 16)
-    lay = ref.Layout(2, 2, 64, 1, 16)
-    lt = T.tl_layout(2, 2, 64, 1, 16, 1)
+    lay = ref.Layout(layers, heads, 64, 1, 16)
+    lt = T.tl_layout(layers, heads, 64, 1, 16, 1)
     st = ctypes.c_int()
     ctx = lib.tl_ctx_create(TEN, len(TEN), FP, len(FP), ctypes.byref(lt), ctypes.byref(st))
     assert ctx and st.value == 0
@@ -111,7 +112,7 @@ def test_each_defence_on_off_restored():
     d_bidx = i64(np.arange(n))
     d_tok = i32(toks.view(np.int32))
     table = i32(wl.page_table(n, n, 3, 1)[None, :])
-    dst = PagedCache(2, n, lay.slab_bytes, DEV)
+    dst = PagedCache(layers, n, lay.slab_bytes, DEV)
     ws_bytes = lib.tl_workspace_bytes(ctx, n)
     ws = torch.empty(ws_bytes, dtype=torch.uint8, device=DEV)
     verd = torch.zeros(n, dtype=torch.uint8, device=DEV)
@@ -129,7 +130,7 @@ def test_each_defence_on_off_restored():
 
     def pages_hold(b, rec):
         p = int(table.cpu()[0, b])
-        for l in range(2):
+        for l in range(layers):
             for kv, t in ((0, dst.k[l]), (1, dst.v[l])):
                 s = 2 * l + kv
                 if t[p].cpu().numpy().tobytes() != rec[po + s * lay.slab_bytes: po + (s + 1) * lay.slab_bytes]:

@@ -2,8 +2,9 @@
 allocate device memory, against tl_load: two calls in a row on the same
 device array, the second with fewer blocks, each with damaged records, must
 give the verdicts and destination caches tl_load gives, byte for byte; both
-are checked against the oracle too. Called through the C ABI (the binding
-only marshals arguments)."""
+are checked against the oracle too. With 3 layers a workgroup restores each
+block and the array stays as it is; with 8 the status words are in it. Called
+through the C ABI (the binding only marshals arguments)."""
 import numpy as np
 import pytest
 import torch
@@ -17,8 +18,8 @@ from tests.gpu_case import DEV, Case, host_layers, i32, i64, log
 pytestmark = pytest.mark.gpu
 
 
-def _run(n, seed, flips, trunc):
-    geom = wl.Geometry(3, 2, 128, 16)  # 8 KiB slabs, 48 KiB records
+def _run(layers, n, seed, flips, trunc):
+    geom = wl.Geometry(layers, 2, 128, 16)  # 8 KiB slabs, records of 16 KiB per layer
     c = Case(geom, n, n + 8, n + 8, seed)
     c.make_src()
     store, st = c.save()
@@ -62,14 +63,15 @@ def _run(n, seed, flips, trunc):
     return vo
 
 
-def test_load_static_equals_load_on_two_calls_the_second_smaller():
+@pytest.mark.parametrize("layers", [3, 8])
+def test_load_static_equals_load_on_two_calls_the_second_smaller(layers):
     rb_meta = 100  # a metadata byte (root mismatch)
     po = 512 + 3000  # a payload byte (segment mismatch), past the 512-byte metadata
-    vo = _run(200, 41, flips=[(3, rb_meta), (150, po), (199, po + 40000)], trunc=[77, 198])
+    vo = _run(layers, 200, 41, flips=[(3, rb_meta), (150, po), (199, po + 40000)], trunc=[77, 198])
     assert vo.count(ref.ACCEPT) == 195 and vo[3] == ref.ROOT and vo[150] == ref.SEGMENT and vo[77] == ref.TRUNCATED
     # the second call leaves the array holding the first call's words past its
     # 60 blocks; its own words are cleared by its first kernel
-    vo = _run(60, 42, flips=[(10, po)], trunc=[59])
+    vo = _run(layers, 60, 42, flips=[(10, po)], trunc=[59])
     assert vo.count(ref.ACCEPT) == 58 and vo[10] == ref.SEGMENT and vo[59] == ref.TRUNCATED
 
 
