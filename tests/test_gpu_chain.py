@@ -476,8 +476,9 @@ def test_device_restore_matches_the_oracle():
     assert n_acc > 0 and n_rej > 0
 
 
-def test_device_restore_in_a_graph_replays_with_new_requests():
-    geom = wl.Geometry(2, 4, 64, 16)
+@pytest.mark.parametrize("layers", [2, 8])  # loads in one kernel, in three
+def test_device_restore_in_a_graph_replays_with_new_requests(layers):
+    geom = wl.Geometry(layers, 4, 64, 16)
     c = Case(geom, 16, 16, 16, seed=70)
     c.make_src()
     store, st = c.save()
@@ -616,7 +617,7 @@ def check_walk(ch, ns, bt, index, keys, handles, hits, parents=None):
 @pytest.mark.parametrize("case", ["complete", "token_holes", "decoys", "key_holes"])
 def test_parallel_walk_equals_the_oracle_walk(case):
     ctx, ns, bt = ctx_bt(16)
-    n_doc = 1300  # longer than a tile (1,024 blocks while chains are few)
+    n_doc = 1300  # 21 tiles of 63 blocks
     docs, _ = stored_docs(ns, bt, 5, n_doc, 90)
     kw = {}
     if case == "token_holes":
@@ -661,25 +662,27 @@ def pad_chains(ctx, ch, bt, extra):
 
 
 @pytest.mark.parametrize("case", ["complete", "key_hole_at_tile_start", "token_hole_at_tile_end",
-                                  "token_hole_at_tile_start", "decoy"])
+                                  "token_hole_at_tile_start", "decoy", "decoy_at_tile_end"])
 def test_parallel_walk_one_long_chain(case):
-    """One chain of 6,100 blocks (the paper corpus is 6,062): its six tiles go
-    to workgroups of their own. Holes and disagreements sit at tile
-    boundaries, where a tile's first block depends on the candidate of the
-    previous tile's last block."""
+    """One chain of 6,100 blocks (the paper corpus is 6,062): its 97 tiles of 63
+    go to wavefronts of their own, or four at a time to the workgroup of the
+    chain. Holes and disagreements sit at tile boundaries well inside, where a
+    tile's first block depends on the candidate of the previous tile's last
+    block."""
     ctx, ns, bt = ctx_bt(16)
-    n_doc = 6100
+    n_doc, tile = 6100, 63
     docs, _ = stored_docs(ns, bt, 1, n_doc, 130)
     kw, want = {}, n_doc
     if case == "key_hole_at_tile_start":
-        kw["skip"], want = {1024}, 1024
+        kw["skip"], want = {16 * tile}, 16 * tile
     if case == "token_hole_at_tile_end":
-        kw["token_skip"] = {1023}
+        kw["token_skip"] = {16 * tile - 1}
     if case == "token_hole_at_tile_start":
-        kw["token_skip"] = {1024}
-    if case == "decoy":
+        kw["token_skip"] = {16 * tile}
+    if case.startswith("decoy"):
+        at = 32 * tile - (case == "decoy_at_tile_end")
         dec = docs[0].copy()
-        dec[2048 * bt:2049 * bt] = wl.tokens(bt, 131)  # same tokens as the document after block 2048
+        dec[at * bt:(at + 1) * bt] = wl.tokens(bt, 131)  # same tokens as the document after that block
         kw["decoys"] = [dec]
     two = TwoIndexes(ctx, ns, bt, docs, cap=32768, **kw)
     req = np.concatenate([docs[0], wl.tokens(7, 132)])
@@ -746,7 +749,7 @@ def test_parallel_walk_with_parents_and_positions():
 
 
 def test_parallel_walk_many_chains():
-    """More chains than four per CU: 256-block tiles, chains of several tiles."""
+    """1,100 chains of up to twelve tiles, three wavefronts for the tiles of each."""
     ctx, ns, bt = ctx_bt(16)
     docs, _ = stored_docs(ns, bt, 4, 700, 95)
     two = TwoIndexes(ctx, ns, bt, docs, cap=8192, token_skip=set(range(5, 2800, 97)))
@@ -800,8 +803,8 @@ def test_parallel_walk_random(seed):
     check_walk(padded, ns, bt, two.index, kp, hp, hitsp)
 
 
-def _device_path_case(seed):
-    geom = wl.Geometry(2, 4, 64, 16)
+def _device_path_case(seed, layers=2):
+    geom = wl.Geometry(layers, 4, 64, 16)
     c = Case(geom, 24, 24, 24, seed=seed)
     c.make_src()
     store, st = c.save()
@@ -848,8 +851,61 @@ def _indexes(c, keys, handles):
     return idx, tidx, d_hk
 
 
-def test_parallel_device_restore_in_a_graph():
-    c, store, bt, keys = _device_path_case(71)
+@pytest.mark.parametrize("call,refused", [("save_blocks", "page"), ("save_blocks", "key"), ("save_blocks", "fingerprint"),
+                                          ("add", "key"), ("add", "fingerprint")])
+def test_device_store_refusals(call, refused):
+    """A block that the save refuses (a page id out of range) stops
+    DeviceStore.save_blocks before anything is indexed; a key or a fingerprint
+    that an index refuses (its first eight bytes are another key's there) stops
+    it and DeviceStore.add at that index, with the other keys of the call in it.
+    The same call without the cause succeeds."""
+    from paper_2609_39358_amd import pipeline
+    geom, n = wl.Geometry(2, 4, 64, 16), 70
+    c = Case(geom, n, n, n, seed=74)
+    c.make_src()
+    store = pipeline.DeviceStore(c.ctx, 128, DEV)
+    store.records.lens.fill_(7)
+    slots = np.random.default_rng(5).permutation(128)[:n]
+    keys, fps = [k.tobytes() for k in c.keys], fingerprints(c.ctx, c.tokens, np.arange(n, dtype=np.uint64))
+    tables = c.t_src.copy()
+    index, what = (store.key_index, keys) if refused == "key" else (store.token_index, fps)
+    if refused == "page":
+        tables[0, 61] = n
+    else:
+        assert (dput(index, [what[61][:31] + bytes([what[61][31] ^ 1])], [9]) == T.TL_INDEX_STORED).all()
+
+    def run():
+        d_slots = torch.from_numpy(slots).to(DEV)
+        if call == "add":
+            return store.add(c.d_keys, c.d_tokens, c.d_bidx, d_slots)
+        return store.save_blocks(c.src, i32(tables), c.d_keys, c.d_tokens, c.d_bidx, d_slots)
+
+    log("device store refuses a", refused, "in", call)
+    with pytest.raises(RuntimeError, match="save refused" if refused == "page" else "index refused"):
+        run()
+    torch.cuda.synchronize()
+    done = [int(s) for s in slots]
+    miss = [T.MISS] * n
+    but = done[:61] + [T.MISS] + done[62:]
+    lens = store.lens.cpu().numpy()
+    stored = refused != "page" and call == "save_blocks"
+    assert (lens[slots] == (c.ctx.record_bytes if stored else 7)).all() and (np.delete(lens, slots) == 7).all()
+    slot_keys = store.slot_keys.cpu().numpy()
+    assert np.array_equal(slot_keys[slots], np.zeros((n, 32), np.uint8) if refused == "page" else c.keys)
+    assert dget(store.key_index, keys) == {"page": miss, "key": but, "fingerprint": done}[refused]
+    assert dget(store.token_index, fps) == {"page": miss, "key": miss, "fingerprint": but}[refused]
+    # without the cause
+    tables = c.t_src
+    store = pipeline.DeviceStore(c.ctx, 128, DEV)
+    st = run()
+    torch.cuda.synchronize()
+    assert st is None or (st.cpu().numpy() == ref.ACCEPT).all()
+    assert dget(store.key_index, keys) == dget(store.token_index, fps) == done
+
+
+@pytest.mark.parametrize("layers", [2, 8])
+def test_parallel_device_restore_in_a_graph(layers):
+    c, store, bt, keys = _device_path_case(71, layers)
     doc = c.tokens.reshape(-1)
     idx, tidx, d_hk = _indexes(c, keys, range(c.n))
     index = ref.index_put({}, keys, range(c.n))
@@ -1060,10 +1116,10 @@ def test_walks_with_tails_equal_the_oracle_walk():
 
 
 def test_long_chains_with_tails_on_both_walk_paths():
-    """Chains of 2,500 full blocks and a partial last one: three tiles each,
-    the tail in the last tile. The walk with its tiles on workgroups of their
-    own and the one-workgroup walk (forced by empty chains) equal the oracle
-    walk, tails included."""
+    """Chains of 2,500 full blocks and a partial last one: forty tiles, the tail
+    in the last one. The walk with its tiles on wavefronts of their own and the
+    one-workgroup walk (forced by empty chains) equal the oracle walk, tails
+    included."""
     ctx, ns, bt = ctx_bt(16)
     docs = [wl.tokens(2500 * 16 + 9, 140), wl.tokens(2100 * 16 + 15, 141)]
     ts = TailStore(ctx, ns, bt, docs)
