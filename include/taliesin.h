@@ -217,7 +217,12 @@ int tl_block_keys_batch(const tl_ctx* ctx, const uint8_t* parents, const void* b
  * TL_BADARG for a misaligned pointer (nothing written); TL_BADARG for a page
  * id outside [0, n_pages) (other than -1 on a page that a partial block
  * leaves out) or an invalid token count (the whole record is written as
- * zeros, so any later load fails). Sec. 2.2 (save after prefill), Fig. 1. */
+ * zeros, so any later load fails). Blocks of one call may name the same record
+ * if they hold the same bytes. A record's bytes are not defined until the call
+ * has completed on its stream. The call issues two kernels, and up to about 25
+ * where records have 8,192 chunk digests or more (their metadata is then hashed
+ * while later chunks are copied), no memset and no allocation: it can be
+ * captured into a HIP graph. Sec. 2.2 (save after prefill), Fig. 1. */
 int tl_save(const tl_ctx* ctx, void* stream, size_t n_blocks, const tl_cache* src,
             const tl_blocks* blocks, const uint64_t* d_record_ptrs, uint8_t* d_status);
 
@@ -230,8 +235,8 @@ int tl_save(const tl_ctx* ctx, void* stream, size_t n_blocks, const tl_cache* sr
  * and root, and d_status as tl_save does; n_pages is the source cache's page
  * count, used to report TL_BADARG. A record is valid only after its seal, and
  * only if every layer range was saved before the seal (stream order). tl_save
- * is exactly tl_save_layers(0, n_layers, TL_SAVE_EXCLUSIVE) followed by
- * tl_save_seal.
+ * writes the same bytes and statuses as tl_save_layers(0, n_layers,
+ * TL_SAVE_EXCLUSIVE) followed by tl_save_seal.
  * flags: 0 or TL_SAVE_SHARED (the same): a kernel with a small footprint
  * (two wavefronts per SIMD) for saves that run while kernels of other
  * streams (the prefill of later layers) keep the device busy; it keeps pace
@@ -268,10 +273,11 @@ int tl_save_seal(const tl_ctx* ctx, void* stream, size_t n_blocks, int64_t n_pag
  * block would have written is zero-filled; pages of -1 entries are untouched.
  * Distinct blocks must not name the same destination page.
  * d_workspace: device, >= tl_workspace_bytes(ctx, n_blocks), 4-byte aligned;
- * its contents need no initialisation. The call issues three kernels and no
- * memset or allocation, so it can be captured into a HIP graph and replayed
- * (the arrays are read at run time: their contents may change between
- * replays). Sec. 2.2, Sec. 3, Sec. 5. */
+ * its contents need no initialisation. The call issues three kernels, or for
+ * small blocks (at most 15 chunks) a single one, one per 2^20 blocks, which
+ * leaves the workspace as it is; no memset and no allocation, so it can be
+ * captured into a HIP graph and replayed (the arrays are read at run time: their
+ * contents may change between replays). Sec. 2.2, Sec. 3, Sec. 5. */
 int tl_load(const tl_ctx* ctx, void* stream, size_t n_blocks, const uint64_t* d_record_ptrs,
             const uint64_t* d_record_lens, const tl_blocks* blocks, const tl_cache* dst,
             uint8_t* d_verdicts, void* d_workspace, size_t workspace_bytes);
@@ -284,8 +290,8 @@ int tl_load(const tl_ctx* ctx, void* stream, size_t n_blocks, const uint64_t* d_
  * device, on the first call whose stream belongs to that device). The call
  * allocates nothing. Every call on one GPU shares that GPU's array: calls
  * that overlap on one GPU (on different streams without ordering) race and
- * must not be issued; calls ordered on a stream are safe, since the first
- * kernel of each call clears the words it uses. Same arguments, checks,
+ * must not be issued; calls ordered on a stream are safe, since each call
+ * clears the words it uses. Same arguments, checks,
  * verdicts and restored bytes as tl_load. TL_ERANGE (nothing enqueued) when
  * n_blocks > TL_LOAD_STATIC_MAX_BLOCKS; TL_EDEVICE if the stream's device
  * or the array's address cannot be found. */
@@ -321,9 +327,9 @@ int tl_index_lookup_prefix(const tl_index* idx, const uint8_t* keys, const uint6
 
 /* ---- a1 + a2 on the device: key chains and a device index ----------------
  * For engines whose token ids are already in HBM. The same chained keys as
- * tl_block_keys (u32 token ids, B = 4 * tokens per block) are computed one
- * chain per lane and looked up, as they are made, in an index held in device
- * memory; tl_chain_stage turns the result into tl_load's inputs. A restore
+ * tl_block_keys (u32 token ids, B = 4 * tokens per block) are computed, a chain
+ * on a workgroup or (thousands of chains) on a lane, and looked up, as they are
+ * made, in an index held in device memory; tl_chain_stage turns the result into tl_load's inputs. A restore
  * (tl_chain_lookup -> tl_chain_stage -> tl_load) then needs no host round
  * trip and can be enqueued on one stream or captured into a graph.
  * Sec. 2.2 (a later request that contains the same block loads its state
@@ -363,8 +369,8 @@ void tl_dindex_destroy(tl_dindex* idx); /* leaves d_mem to the caller; NULL is a
  * up to 256). */
 size_t tl_dindex_workspace_bytes(size_t n);
 /* Insert or overwrite n keys (device [n][32]) with handles (device [n]).
- * d_status (device [n] or NULL) receives TL_INDEX_*. Three kernels, no
- * memset; d_workspace needs no initialisation. */
+ * d_status (device [n] or NULL) receives TL_INDEX_*. Three kernels, or one for
+ * up to 256 keys, no memset; d_workspace needs no initialisation. */
 int tl_dindex_put(tl_dindex* idx, void* stream, size_t n, const uint8_t* d_keys,
                   const uint64_t* d_handles, uint8_t* d_status, void* d_workspace,
                   size_t workspace_bytes);
@@ -498,12 +504,13 @@ int tl_file_drop_cache(tl_file* f);
  * kernel launch is bracketed by two HIP events recorded on the launch stream.
  * tl_timing returns the previous setting. tl_timing_read waits for the
  * recorded events of one kernel, returns the summed milliseconds and the
- * number of launches, and forgets them. Disabled by default; costs two event
- * records per launch when enabled. */
+ * number of launches, and forgets them (the kernels that end a save, and those
+ * of one tl_chain_lookup_par, count as one). Disabled by default; costs two
+ * event records per launch when enabled. */
 #define TL_KERNEL_SAVE_SEG 0
 #define TL_KERNEL_SAVE_META 1
 #define TL_KERNEL_LOAD_INIT 2
-#define TL_KERNEL_LOAD_MAIN 3
+#define TL_KERNEL_LOAD_MAIN 3 /* also the single kernel of a load of small blocks */
 #define TL_KERNEL_LOAD_FINAL 4
 #define TL_KERNEL_CHAIN 5 /* tl_chain_lookup */
 #define TL_KERNEL_STAGE 6 /* tl_chain_stage */
