@@ -185,6 +185,40 @@ def test_rejected_blocks_at_tile_edges(layers, n, bad):
     assert sorted(b for b in range(n) if vo[b] != ref.ACCEPT) == sorted(bad)
 
 
+# Requests whose ends are not stored: runs of missing blocks without pages among
+# damaged ones with them, with up to 8 table entries per block and with more; a
+# damaged block may have pages in one layer group or on its last page alone, and
+# a missing one may have pages too.
+@pytest.mark.parametrize("groups,ppb", [(1, 1), (2, 1), (2, 4), (1, 9), (3, 3)])
+def test_rejected_blocks_among_missing_ones(groups, ppb):
+    layers, n = 8, 1100 if ppb == 1 else 300
+    geom = wl.Geometry(layers, 1, 64, 8, "bf16", (0,) * layers, tuple(l % groups for l in range(layers)), ppb)
+    c = Case(geom, n, n * ppb, n * ppb + 3, seed=43)
+    c.make_src()
+    store, _ = c.save()
+    recs = [bytearray(r.tobytes()) for r in store.buf.cpu().numpy()]
+    t_dst, ptrs = c.t_dst.copy(), store.ptrs.clone()
+    gone = [b for b in range(n) if b % 100 >= 60]
+    for b in gone:
+        recs[b] = None
+        ptrs[b] = 0
+        if b % 100 != 77:
+            t_dst[:, b * ppb:(b + 1) * ppb] = -1
+    for b in range(3, n, 50):
+        if recs[b] is not None:
+            recs[b][90] ^= 2
+            if b % 100 < 50:  # one group's last page is all that is restored
+                t_dst[:, b * ppb:(b + 1) * ppb - 1] = -1
+                t_dst[:-1, (b + 1) * ppb - 1] = -1
+    store2 = upload_records([r or b"" for r in recs], c.lay.record_bytes)
+    ptrs += (store2.ptrs - store.ptrs) * (ptrs != 0)
+    dst = random_fill(PagedCache(layers, n * ppb + 3, c.stride, DEV), 3)
+    hk0, hv0 = host_layers(dst)
+    log("rejected among missing", groups, "groups", ppb, "pages", n, "blocks")
+    vo = check_restore(c, [None if r is None else bytes(r) for r in recs], ptrs, store2.lens, t_dst, dst, hk0, hv0)
+    assert [b for b in range(n) if vo[b] == ref.MISSING] == gone and ref.ROOT in vo and ref.ACCEPT in vo
+
+
 # Slabs of a 64-row chunk and a ragged one, in blocks of 4 chunks (a workgroup
 # per block) and of 12 and 20, and of 1,024 of which 8 have 8,192 (whole chunks in
 # flight), with pages that are not restored (nor read) and damage in a chunk of
